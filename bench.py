@@ -82,7 +82,7 @@ def load_traffic(workload: str, launch=None):
 
 def launch_shapes(H, L, db):
     """The launch decisions in force for lattice L and where each came from:
-    Dslash shape (1 = one site per work-item, 2/4 = direction split) and
+    Dslash shape (1 = one site per work-item, 2 = two wavefronts, 4 = one per hop) and
     link form (reals read per SU(3) link: 12 = two rows, 10 = row 0 and
     column 2), streaming (non-temporal link loads and output stores), site
     order (0 linear, 1 tiled by z-planes, n tiled by y-blocks of n 64-site

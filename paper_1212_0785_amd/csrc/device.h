@@ -371,7 +371,30 @@ struct Lat {
   // the z-planes are not whole chunks and the walk takes the chunks of the
   // t-slices instead).
   int tiled, plane, slice, tile_r, tile_t, tile_y;
+  // Division by L0 / 2, L1 and L2 as a multiplication (div_by): the site
+  // index is split into coordinates at the head of every kernel, and three
+  // dependent integer divisions cost a wavefront ~0.3 us before its first
+  // load.
+  unsigned mul[3];
+  int shift[3];
 };
+
+// Multiplier and shift with n / d == mulhi(n, mul) >> shift for all
+// 0 <= n < 2^31 (1 < d < 2^31): with l = ceil(log2 d) and mul =
+// ceil(2^(31 + l) / d) < 2^32, mul d - 2^(31 + l) < d <= 2^l, so the error
+// n (mul d - 2^(31 + l)) / (d 2^(31 + l)) stays below 1 / d.  d = 1 has
+// mul = 0, which div_by takes as n itself.
+inline void div_magic(int d, unsigned* mul, int* shift) {
+  if (d <= 1) {
+    *mul = 0;
+    *shift = 0;
+    return;
+  }
+  int l = 0;
+  while ((1LL << l) < d) ++l;
+  *mul = (unsigned)(((1ULL << (31 + l)) + (unsigned)d - 1) / (unsigned)d);
+  *shift = l - 1;
+}
 
 inline Lat to_lat(const LatArg& a) {
   Lat g;
@@ -379,7 +402,15 @@ inline Lat to_lat(const LatArg& a) {
   g.Vh = a.Vh;
   g.stride = a.stride;
   g.tiled = g.plane = g.slice = g.tile_r = g.tile_t = g.tile_y = 0;
+  const int d[3] = {a.L[0] / 2, a.L[1], a.L[2]};
+  for (int k = 0; k < 3; ++k) div_magic(d[k], &g.mul[k], &g.shift[k]);
   return g;
+}
+
+// n / (L0 / 2), n / L1, n / L2 for K = 0, 1, 2 (0 <= n < 2^31).
+template <int K>
+__device__ __forceinline__ int div_by(const Lat& g, int n) {
+  return g.mul[K] ? (int)(__umulhi((unsigned)n, g.mul[K]) >> g.shift[K]) : n;
 }
 
 struct Site {
@@ -389,16 +420,14 @@ struct Site {
 
 __device__ __forceinline__ Site cb_site(const Lat& g, int par, int s) {
   Site st;
-  int i0 = 2 * s;
-  int x0 = i0 % g.L[0];
-  int r = i0 / g.L[0];
-  st.c[1] = r % g.L[1];
-  r /= g.L[1];
-  st.c[2] = r % g.L[2];
-  st.c[3] = r / g.L[2];
-  int odd = (par ^ st.c[1] ^ st.c[2] ^ st.c[3]) & 1;
-  st.c[0] = x0 + odd;
-  st.lex = i0 + odd;
+  const int hx = g.L[0] >> 1;
+  const int r = div_by<0>(g, s), r1 = div_by<1>(g, r), t = div_by<2>(g, r1);
+  st.c[1] = r - r1 * g.L[1];
+  st.c[2] = r1 - t * g.L[2];
+  st.c[3] = t;
+  const int odd = (par ^ st.c[1] ^ st.c[2] ^ st.c[3]) & 1;
+  st.c[0] = 2 * (s - r * hx) + odd;
+  st.lex = 2 * s + odd;
   return st;
 }
 
@@ -422,13 +451,10 @@ __device__ __forceinline__ int neighbour_lex(const Lat& g, const Site& st, bool*
 }
 
 __device__ __forceinline__ int parity_of_lex(const Lat& g, int lex) {
-  int x = lex % g.L[0];
-  int r = lex / g.L[0];
-  int y = r % g.L[1];
-  r /= g.L[1];
-  int z = r % g.L[2];
-  int t = r / g.L[2];
-  return (x + y + z + t) & 1;
+  // the pair of sites 2s, 2s + 1 shares y, z and t
+  const int r = div_by<0>(g, lex >> 1), r1 = div_by<1>(g, r), t = div_by<2>(g, r1);
+  const int y = r - r1 * g.L[1], z = r1 - t * g.L[2];
+  return (lex + y + z + t) & 1;
 }
 
 // The 8 XCDs of an MI355X take workgroups round-robin.  This remaps the
@@ -519,11 +545,15 @@ struct SpF64 {
     v2d t = gld<v2d>(base, k * stride + s);
     return {t.x, t.y};
   }
+  template <bool NT = false>
+  __device__ static void store_one(void* base, int stride, int s, int k, cx<R> v) {
+    gput<NT>(base, k * stride + s, v2d{v.re, v.im});
+  }
   // components 3*part .. 3*part+2 of site s
   template <bool NT = false>
   __device__ static void store_part(void* base, int stride, int s, int part, const cx<R>* v) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) gput<NT>(base, (3 * part + c) * stride + s, v2d{v[c].re, v[c].im});
+    for (int c = 0; c < 3; ++c) store_one<NT>(base, stride, s, 3 * part + c, v[c]);
   }
 };
 
@@ -548,9 +578,13 @@ struct SpF32 {
     return {t.x, t.y};
   }
   template <bool NT = false>
+  __device__ static void store_one(void* base, int stride, int s, int k, cx<R> v) {
+    gput<NT>(base, k * stride + s, v2f{v.re, v.im});
+  }
+  template <bool NT = false>
   __device__ static void store_part(void* base, int stride, int s, int part, const cx<R>* v) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) gput<NT>(base, (3 * part + c) * stride + s, v2f{v[c].re, v[c].im});
+    for (int c = 0; c < 3; ++c) store_one<NT>(base, stride, s, 3 * part + c, v[c]);
   }
 };
 
@@ -591,16 +625,14 @@ struct SpF16 {
     v2f t = __builtin_convertvector(gld<v2h>(base, k * stride + s), v2f);
     return {t.x * f, t.y * f};
   }
-  // components 3*part .. 3*part+2 of site s, with the site's max |re|,|im|
-  // m computed by the caller over all 12 components (part 0 writes it)
+  // component k of site s, scaled by inv, and the site's scale m itself
   template <bool NT = false>
-  __device__ static void store_part_scaled(void* base, int stride, int s, int part, const cx<R>* v, float m) {
-    m = live_scale(m);
-    const float inv = m > 0.f ? 1.f / m : 0.f;
-    if (part == 0) gput<NT>(base, 12 * stride + s, m);
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      gput<NT>(base, (3 * part + c) * stride + s, __builtin_convertvector((v2f{v[c].re * inv, v[c].im * inv}), v2h));
+  __device__ static void store_one_scaled(void* base, int stride, int s, int k, cx<R> v, float inv) {
+    gput<NT>(base, k * stride + s, __builtin_convertvector((v2f{v.re * inv, v.im * inv}), v2h));
+  }
+  template <bool NT = false>
+  __device__ static void store_scale(void* base, int stride, int s, float m) {
+    gput<NT>(base, 12 * stride + s, m);
   }
 };
 
@@ -625,10 +657,13 @@ struct SpBF16 {
     return {bf16_to_f(w & 0xffffu), bf16_to_f(w >> 16)};
   }
   template <bool NT = false>
+  __device__ static void store_one(void* base, int stride, int s, int k, cx<R> v) {
+    gput<NT>(base, k * stride + s, f_to_bf16(v.re) | (f_to_bf16(v.im) << 16));
+  }
+  template <bool NT = false>
   __device__ static void store_part(void* base, int stride, int s, int part, const cx<R>* v) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-      gput<NT>(base, (3 * part + c) * stride + s, f_to_bf16(v[c].re) | (f_to_bf16(v[c].im) << 16));
+    for (int c = 0; c < 3; ++c) store_one<NT>(base, stride, s, 3 * part + c, v[c]);
   }
 };
 

@@ -163,21 +163,18 @@ __global__ void __launch_bounds__(kBlock) HMC_DSLASH_WAVES k_dslash(Lat g, int o
   }
 }
 
-// Direction-split variant: a block covers 64 sites with NW wavefronts
-// (NW = 2 or 4); wave w computes the hops along directions
-// w*4/NW .. (w+1)*4/NW - 1 for those sites and parks its partial sum in
-// LDS; after a barrier each work-item combines the NW partials of 12/NW of
-// the 12 components of one site (coalesced stores).  NW times the
-// wavefronts of the one-site-per-work-item kernel at the same registers per
-// work-item, and 1/NW of its serial hop chain per wavefront.
-template <class SP, class LK, bool DAG, int EPI, bool BATCH, int NW>
-__global__ void __launch_bounds__(NW * 64) k_dslash_split(Lat g, int out_par, const DslashArgs* __restrict__ table,
-                                                          DslashArgs one, int j) {
+// Two-way direction split: a block of two wavefronts covers 64 sites;
+// wavefront w computes the hops along directions 2w and 2w + 1 and parks its
+// partial sum in LDS; after a barrier each work-item combines the two
+// partials of six of the 12 components of one site (coalesced stores).
+// Twice the wavefronts of the one-site-per-work-item kernel at the same
+// registers per work-item, and half of its serial hop chain.
+template <class SP, class LK, bool DAG, int EPI, bool BATCH>
+__global__ void __launch_bounds__(128) k_dslash_split(Lat g, int out_par, const DslashArgs* __restrict__ table,
+                                                      DslashArgs one, int j) {
   using R = typename SP::R;
   constexpr int kSites = 64;
-  constexpr int kDirs = 4 / NW;    // directions per wavefront
-  constexpr int kParts = 4 / NW;   // groups of 3 components per work-item in the combine
-  __shared__ cx<R> part[NW][12][kSites];
+  __shared__ cx<R> part[2][12][kSites];
   const DslashArgs* ep;
   if constexpr (BATCH)
     ep = table + blockIdx.y;
@@ -186,7 +183,7 @@ __global__ void __launch_bounds__(NW * 64) k_dslash_split(Lat g, int out_par, co
   const DslashArgs& e = *ep;
   const int label = e.iter0 + j + (e.label_base ? *(const HMC_GLOBAL int*)e.label_base : 0);
   if (e.stop_at && label >= *(const HMC_GLOBAL int*)e.stop_at) return;
-  alpha_prologue<NW>(e, label);
+  alpha_prologue<2>(e, label);
   const int b = xcd_remap(blockIdx.x, gridDim.x);
   const int w = threadIdx.x >> 6;  // wave index (uniform per wave)
   const int ls = threadIdx.x & (kSites - 1);
@@ -197,47 +194,31 @@ __global__ void __launch_bounds__(NW * 64) k_dslash_split(Lat g, int out_par, co
     for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
     if (s < g.Vh) {
       const Site st = cb_site(g, out_par, s);
-      if constexpr (NW == 4) {
-        switch (w) {
-          case 0: hop_dir<SP, LK, 0, DAG>(g, st, out_par, s, e.U, e.in, acc); break;
-          case 1: hop_dir<SP, LK, 1, DAG>(g, st, out_par, s, e.U, e.in, acc); break;
-          case 2: hop_dir<SP, LK, 2, DAG>(g, st, out_par, s, e.U, e.in, acc); break;
-          default: hop_dir<SP, LK, 3, DAG>(g, st, out_par, s, e.U, e.in, acc); break;
-        }
+      if (w == 0) {
+        hop_dir<SP, LK, 0, DAG>(g, st, out_par, s, e.U, e.in, acc);
+        hop_dir<SP, LK, 1, DAG>(g, st, out_par, s, e.U, e.in, acc);
       } else {
-        if (w == 0) {
-          hop_dir<SP, LK, 0, DAG>(g, st, out_par, s, e.U, e.in, acc);
-          hop_dir<SP, LK, 1, DAG>(g, st, out_par, s, e.U, e.in, acc);
-        } else {
-          hop_dir<SP, LK, 2, DAG>(g, st, out_par, s, e.U, e.in, acc);
-          hop_dir<SP, LK, 3, DAG>(g, st, out_par, s, e.U, e.in, acc);
-        }
+        hop_dir<SP, LK, 2, DAG>(g, st, out_par, s, e.U, e.in, acc);
+        hop_dir<SP, LK, 3, DAG>(g, st, out_par, s, e.U, e.in, acc);
       }
     }
 #pragma unroll
     for (int k = 0; k < 12; ++k) part[w][k][ls] = acc[k];
   }
-  (void)kDirs;
   __syncthreads();
-  // work-item (ls, w) now owns components 3*kParts*w .. 3*kParts*(w+1)-1 of site s
+  // work-item (ls, w) now owns components 6 w .. 6 w + 5 of site s
   double nrm[1] = {0.0};
-  cx<R> o[3 * kParts];
+  cx<R> o[6];
   const bool active = s < g.Vh;
   if (active) {
 #pragma unroll
-    for (int c = 0; c < 3 * kParts; ++c) {
-      const int k = 3 * kParts * w + c;
-      cx<R> t = part[0][k][ls];
-#pragma unroll
-      for (int q = 1; q < NW; ++q) t = t + part[q][k][ls];
-      o[c] = t;
-    }
+    for (int c = 0; c < 6; ++c) o[c] = part[0][6 * w + c][ls] + part[1][6 * w + c][ls];
     if (EPI != EPI_PLAIN) {
       const R a = (R)e.a, bb = (R)e.b;
 #pragma unroll
-      for (int c = 0; c < 3 * kParts; ++c) {
+      for (int c = 0; c < 6; ++c) {
         if (e.y) {
-          const cx<R> y = SP::load_one(e.y, g.stride, s, 3 * kParts * w + c);
+          const cx<R> y = SP::load_one(e.y, g.stride, s, 6 * w + c);
           o[c] = {fma(bb, o[c].re, a * y.re), fma(bb, o[c].im, a * y.im)};
         } else {
           o[c] = bb * o[c];
@@ -247,38 +228,218 @@ __global__ void __launch_bounds__(NW * 64) k_dslash_split(Lat g, int out_par, co
     if (EPI == EPI_CG) {
       const R al = (R)(*(const HMC_GLOBAL double*)e.alpha_in);
 #pragma unroll
-      for (int c = 0; c < 3 * kParts; ++c) {
-        const cx<R> rv = SP::load_one(e.r, g.stride, s, 3 * kParts * w + c);
+      for (int c = 0; c < 6; ++c) {
+        const cx<R> rv = SP::load_one(e.r, g.stride, s, 6 * w + c);
         o[c] = {fma(-al, o[c].re, rv.re), fma(-al, o[c].im, rv.im)};
       }
     }
     if (EPI == EPI_AXPY_NORM || EPI == EPI_CG)
 #pragma unroll
-      for (int c = 0; c < 3 * kParts; ++c) nrm[0] += (double)o[c].re * o[c].re + (double)o[c].im * o[c].im;
+      for (int c = 0; c < 6; ++c) nrm[0] += (double)o[c].re * o[c].re + (double)o[c].im * o[c].im;
   }
   if constexpr (SP::kScaled) {
     // the per-site scale needs the largest |re|, |im| over all 12 components
-    __shared__ float smax[NW][kSites];
+    __shared__ float smax[2][kSites];
     float m = 0.f;
     if (active)
 #pragma unroll
-      for (int c = 0; c < 3 * kParts; ++c) m = fmaxf(m, fmaxf(fabsf((float)o[c].re), fabsf((float)o[c].im)));
+      for (int c = 0; c < 6; ++c) m = fmaxf(m, fmaxf(fabsf((float)o[c].re), fabsf((float)o[c].im)));
+    smax[w][ls] = m;
+    __syncthreads();
+    m = SP::live_scale(fmaxf(smax[0][ls], smax[1][ls]));
+    const float inv = m > 0.f ? 1.f / m : 0.f;
+    if (active) {
+      if (w == 0) SP::template store_scale<LK::kStream>(e.out, g.stride, s, m);
+#pragma unroll
+      for (int c = 0; c < 6; ++c) SP::template store_one_scaled<LK::kStream>(e.out, g.stride, s, 6 * w + c, o[c], inv);
+    }
+  } else {
+    if (active)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) SP::template store_one<LK::kStream>(e.out, g.stride, s, 6 * w + c, o[c]);
+  }
+  if (EPI == EPI_AXPY_NORM || EPI == EPI_CG) {
+    block_sum<1, 2>(nrm);
+    double* dst = e.partial_pp[0] ? e.partial_pp[(label + 1) & 1] : e.partial;
+    if (threadIdx.x == 0) ((HMC_GLOBAL double*)dst)[b] = nrm[0];
+  }
+}
+
+// One hop: uh = U h (forward) or U^dag h (backward), h the two projected
+// spin components of the neighbour's spinor, with the time-boundary sign.
+template <class SP, class LK, int MU, int DIR, bool DAG>
+__device__ __forceinline__ void one_hop(const Lat& g, const Site& st, int out_par, int s, const void* U,
+                                        const void* in, cx<typename SP::R>* uh) {
+  using R = typename SP::R;
+  constexpr int SIG = (DIR > 0) == DAG ? +1 : -1;
+  bool wrap;
+  const int sn = neighbour_lex<MU, DIR>(g, st, &wrap) >> 1;
+  cx<R> psi[12], h[6];
+  SP::load(in, g.stride, sn, psi);
+  const mat3<R> u = DIR > 0 ? LK::load(U, g.stride, MU, out_par, s) : LK::load(U, g.stride, MU, out_par ^ 1, sn);
+  spin_project<MU, SIG>(psi, h);
+  if (MU == 3) {
+    const R sg = wrap ? R(-1) : R(1);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) h[k] = sg * h[k];
+  }
+  if (DIR > 0) {
+    mv(u, h, uh);
+    mv(u, h + 3, uh + 3);
+  } else {
+    mdv(u, h, uh);
+    mdv(u, h + 3, uh + 3);
+  }
+}
+
+// Adds hop (MU, SIG)'s share of spin component SPIN, colour c, to acc.
+template <int MU, int SIG, int SPIN, typename R>
+__device__ __forceinline__ cx<R> hop_share(cx<R> acc, const cx<R> (*h)[64], int c, int ls) {
+  if (SPIN == 0) return acc + h[c][ls];
+  if (SPIN == 1) return acc + h[3 + c][ls];
+  const bool first = MU == 0 || MU == 1 ? SPIN == 3 : SPIN == 2;  // from h0, else from h1
+  const cx<R> v = h[first ? c : 3 + c][ls];
+  if (MU == 0) return acc + (SIG > 0 ? mul_mi(v) : mul_i(v));
+  if (MU == 1) return (SPIN == 2) == (SIG > 0) ? acc + v : acc - v;
+  if (MU == 2) return acc + ((SPIN == 2) == (SIG > 0) ? mul_mi(v) : mul_i(v));
+  return SIG > 0 ? acc + v : acc - v;
+}
+
+// Component (SPIN, c) of D psi from the eight parked half spinors, in hop order.
+template <bool DAG, int SPIN, typename R>
+__device__ __forceinline__ cx<R> hops_combine(const cx<R> (*half)[6][64], int c, int ls) {
+  constexpr int SF = DAG ? +1 : -1, SB = -SF;
+  cx<R> t = {R(0), R(0)};
+  t = hop_share<0, SF, SPIN>(t, half[0], c, ls);
+  t = hop_share<0, SB, SPIN>(t, half[1], c, ls);
+  t = hop_share<1, SF, SPIN>(t, half[2], c, ls);
+  t = hop_share<1, SB, SPIN>(t, half[3], c, ls);
+  t = hop_share<2, SF, SPIN>(t, half[4], c, ls);
+  t = hop_share<2, SB, SPIN>(t, half[5], c, ls);
+  t = hop_share<3, SF, SPIN>(t, half[6], c, ls);
+  t = hop_share<3, SB, SPIN>(t, half[7], c, ls);
+  return t;
+}
+
+// Four-way direction split, one wavefront per hop: a block of eight
+// wavefronts covers 64 sites; wavefront 2 mu (2 mu + 1) loads the forward
+// (backward) neighbour along mu, and parks the six components of the
+// projected, link-multiplied spinor in LDS (six, not the twelve of a full
+// partial sum: 48 KB in FP64).  After one barrier the wavefronts rebuild and
+// add the eight hops, two or one of the twelve components per work-item.
+//
+// What bounds a hop on a small lattice is the latency of its loads (the
+// one-site kernel waits for eight rounds of them, one after the other); here
+// every load of a site is in flight at once, 98 VGPRs per work-item in FP64.
+// Mhat (two hops), against the same split with one wavefront per direction
+// and two rounds of loads: FP64 8^4 9.9 -> 8.9 us (one-site 16.8), 12^3x24
+// 14.9 -> 13.3 (21.6), 16^3x32 32.2 -> 29.9 (34.6; two-way 31.1); FP32
+// 16^3x32 19.6 -> 17.5, FP16 14.9 -> 14.1, BF16 13.7 -> 12.7; FP64 24^3x48
+// with streaming 161 -> 158.
+constexpr int kHopThreads = 8 * 64;
+
+template <class SP, class LK, bool DAG, int EPI, bool BATCH>
+__global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par, const DslashArgs* __restrict__ table,
+                                                     DslashArgs one, int j) {
+  using R = typename SP::R;
+  constexpr int kSites = 64;
+  __shared__ cx<R> half[8][6][kSites];
+  const DslashArgs* ep;
+  if constexpr (BATCH)
+    ep = table + blockIdx.y;
+  else
+    ep = &one;
+  const DslashArgs& e = *ep;
+  const int label = e.iter0 + j + (e.label_base ? *(const HMC_GLOBAL int*)e.label_base : 0);
+  if (e.stop_at && label >= *(const HMC_GLOBAL int*)e.stop_at) return;
+  alpha_prologue<8>(e, label);
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ls = threadIdx.x & (kSites - 1);
+  const int s = b * kSites + ls;
+  const bool active = s < g.Vh;
+  // wavefront w combines spin w % 4, colours 0 and 1 (w < 4) or 2 (w >= 4)
+  const int spin = w & 3, c0 = w < 4 ? 0 : 2, nc = w < 4 ? 2 : 1;
+  cx<R> yv[2], rv[2];
+  if (active) {
+    // the epilogue's inputs are requested with the hop's, not after it
+    if (EPI != EPI_PLAIN && e.y)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (q < nc) yv[q] = SP::load_one(e.y, g.stride, s, 3 * spin + c0 + q);
+    if (EPI == EPI_CG)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (q < nc) rv[q] = SP::load_one(e.r, g.stride, s, 3 * spin + c0 + q);
+    const Site st = cb_site(g, out_par, s);
+    cx<R> uh[6];
+    switch (w) {
+      case 0: one_hop<SP, LK, 0, +1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+      case 1: one_hop<SP, LK, 0, -1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+      case 2: one_hop<SP, LK, 1, +1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+      case 3: one_hop<SP, LK, 1, -1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+      case 4: one_hop<SP, LK, 2, +1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+      case 5: one_hop<SP, LK, 2, -1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+      case 6: one_hop<SP, LK, 3, +1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+      default: one_hop<SP, LK, 3, -1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) half[w][k][ls] = uh[k];
+  }
+  __syncthreads();
+  double nrm[1] = {0.0};
+  cx<R> o[2];
+  if (active) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (q >= nc) break;
+      const int c = c0 + q;
+      switch (spin) {
+        case 0: o[q] = hops_combine<DAG, 0>(half, c, ls); break;
+        case 1: o[q] = hops_combine<DAG, 1>(half, c, ls); break;
+        case 2: o[q] = hops_combine<DAG, 2>(half, c, ls); break;
+        default: o[q] = hops_combine<DAG, 3>(half, c, ls); break;
+      }
+      if (EPI != EPI_PLAIN) {
+        const R a = (R)e.a, bb = (R)e.b;
+        if (e.y)
+          o[q] = {fma(bb, o[q].re, a * yv[q].re), fma(bb, o[q].im, a * yv[q].im)};
+        else
+          o[q] = bb * o[q];
+      }
+      if (EPI == EPI_CG) {
+        const R al = (R)(*(const HMC_GLOBAL double*)e.alpha_in);
+        o[q] = {fma(-al, o[q].re, rv[q].re), fma(-al, o[q].im, rv[q].im)};
+      }
+      if (EPI == EPI_AXPY_NORM || EPI == EPI_CG)
+        nrm[0] += (double)o[q].re * o[q].re + (double)o[q].im * o[q].im;
+    }
+  }
+  if constexpr (SP::kScaled) {
+    __shared__ float smax[8][kSites];
+    float m = 0.f;
+    if (active)
+      for (int q = 0; q < 2; ++q)
+        if (q < nc) m = fmaxf(m, fmaxf(fabsf((float)o[q].re), fabsf((float)o[q].im)));
     smax[w][ls] = m;
     __syncthreads();
     m = smax[0][ls];
 #pragma unroll
-    for (int q = 1; q < NW; ++q) m = fmaxf(m, smax[q][ls]);
-    if (active)
-#pragma unroll
-      for (int q = 0; q < kParts; ++q)
-        SP::template store_part_scaled<LK::kStream>(e.out, g.stride, s, kParts * w + q, o + 3 * q, m);
+    for (int q = 1; q < 8; ++q) m = fmaxf(m, smax[q][ls]);
+    m = SP::live_scale(m);
+    const float inv = m > 0.f ? 1.f / m : 0.f;
+    if (active) {
+      if (w == 7) SP::template store_scale<LK::kStream>(e.out, g.stride, s, m);
+      for (int q = 0; q < 2; ++q)
+        if (q < nc) SP::template store_one_scaled<LK::kStream>(e.out, g.stride, s, 3 * spin + c0 + q, o[q], inv);
+    }
   } else {
     if (active)
-#pragma unroll
-      for (int q = 0; q < kParts; ++q) SP::template store_part<LK::kStream>(e.out, g.stride, s, kParts * w + q, o + 3 * q);
+      for (int q = 0; q < 2; ++q)
+        if (q < nc) SP::template store_one<LK::kStream>(e.out, g.stride, s, 3 * spin + c0 + q, o[q]);
   }
   if (EPI == EPI_AXPY_NORM || EPI == EPI_CG) {
-    block_sum<1, NW>(nrm);
+    block_sum<1, 8>(nrm);
     double* dst = e.partial_pp[0] ? e.partial_pp[(label + 1) & 1] : e.partial;
     if (threadIdx.x == 0) ((HMC_GLOBAL double*)dst)[b] = nrm[0];
   }
@@ -289,7 +450,7 @@ static hipError_t launch_typed(hmc_prec prec, int dagger, int epi, const LatArg&
                                const DslashArgs* table, int nbatch, const DslashArgs& one, hipStream_t st, int j,
                                KernelEvents ev) {
   Lat g = to_lat(ga);
-  const int shape = one.shape ? one.shape : dslash_shape(ga, prec);
+  const int shape = one.shape ? one.shape : dslash_run_shape(ga, prec);
   const int order = shape == 1 ? dslash_tiled_order(ga, prec) : 0;
   if (order) {
     g.tiled = 1;
@@ -299,9 +460,8 @@ static hipError_t launch_typed(hmc_prec prec, int dagger, int epi, const LatArg&
     g.tile_t = ga.L[3] / 8;
     g.tile_y = order == 1 ? g.tile_r : order;  // 0: chunks of the t-slices
   }
-  const int ways = shape == 1 ? 0 : shape;
   const dim3 grid(dslash_shape_blocks(ga.Vh, shape), nbatch);
-  const dim3 block(ways ? 64 * ways : kBlock);
+  const dim3 block(shape == 4 ? kHopThreads : shape == 2 ? 128 : kBlock);
   // The tiled order may reserve LDS it does not use: 54,000 bytes per block
   // leave room for two blocks per CU (2 wavefronts per SIMD), so an XCD's
   // wavefronts in flight span a few (z, t) rows instead of dozens and the
@@ -314,10 +474,10 @@ static hipError_t launch_typed(hmc_prec prec, int dagger, int epi, const LatArg&
   hipExtLaunchKernelGGL(KERNEL, grid, block, lds_cap, st, ev.start, ev.stop, 0, g, out_par, table, one, j)
 #define HMC_DS_B(D, E, B)                                  \
   do {                                                     \
-    if (ways == 4)                                         \
-      HMC_LAUNCH((k_dslash_split<SP, LK, D, E, B, 4>));    \
-    else if (ways == 2)                                    \
-      HMC_LAUNCH((k_dslash_split<SP, LK, D, E, B, 2>));    \
+    if (shape == 4)                                        \
+      HMC_LAUNCH((k_dslash_hops<SP, LK, D, E, B>));        \
+    else if (shape == 2)                                   \
+      HMC_LAUNCH((k_dslash_split<SP, LK, D, E, B>));       \
     else                                                   \
       HMC_LAUNCH((k_dslash<SP, LK, D, E, B>));             \
   } while (0)

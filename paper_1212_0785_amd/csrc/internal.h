@@ -34,8 +34,8 @@ inline int blas_blocks(int Vh) {
 inline int site_blocks(int Vh) { return ceil_div(Vh, kThreads); }
 
 // Launch shapes and link forms (tune.cpp).  Dslash shape: 1 = one site per
-// work-item (256 sites per block), 2 / 4 = direction split with that many
-// wavefronts per 64-site group.  Staple-force shape: 0 = one link per
+// work-item (256 sites per block), 2 = two wavefronts per 64-site group (two
+// directions each), 4 = eight (one hop each).  Staple-force shape: 0 = one link per
 // work-item, 1 = plane split.  Link form: the reals read per link (LinkForm).
 // Each is decided by the environment override, else the tuning table, else
 // the built-in rule.
@@ -83,7 +83,14 @@ inline bool tiled_order_valid(const LatArg& g, int order = 1) {
 // The form a kernel reads: the compact one on SU(3) links, else all entries.
 inline int link_form_for(bool su3, int compact) { return su3 ? compact : (int)LINK_FULL; }
 inline int dslash_shape_blocks(int Vh, int shape) { return shape == 1 ? site_blocks(Vh) : ceil_div(Vh, kThreads / 4); }
-inline int dslash_blocks(const LatArg& g, hmc_prec prec) { return dslash_shape_blocks(g.Vh, dslash_shape(g, prec)); }
+// The shape a launch runs: a lattice of fewer sites than one block of the
+// one-site shape has one wavefront per hop whatever the choice says (4^4,
+// Mhat: 8.8 us against 13.2 us, of which two launches take most).
+inline int dslash_run_shape(int Vh, int choice) { return Vh < kThreads ? 4 : choice; }
+inline int dslash_run_shape(const LatArg& g, hmc_prec prec) { return dslash_run_shape(g.Vh, dslash_shape(g, prec)); }
+inline int dslash_blocks(const LatArg& g, hmc_prec prec) {
+  return dslash_shape_blocks(g.Vh, dslash_run_shape(g, prec));
+}
 // Largest block count (and Dslash-epilogue partial count) of any shape.
 inline int dslash_blocks_max(int Vh) { return ceil_div(Vh, kThreads / 4); }
 // Tuning table: -1 when absent; load/save return entries read/written or -1.

@@ -65,7 +65,7 @@ size_t carve_request(char* base, const LatArg& g, int prec, SolveVecs* v, void**
   Carve c(base);
   const int Vh = g.Vh;
   const size_t h64 = half_bytes(Vh, HMC_F64);
-  const int shape = dslash_shape(g, (hmc_prec)prec);
+  const int shape = dslash_run_shape(g, (hmc_prec)prec);
   const int nbD = dslash_shape_blocks(Vh, shape), nbR = blas_blocks(Vh);
   SolveVecs t{};
   SolveVecs& s = v ? *v : t;
@@ -96,7 +96,7 @@ size_t carve_request(char* base, const LatArg& g, int prec, SolveVecs* v, void**
   s.nbD = nbD;
   s.nbR = nbR;
   s.shape = shape;
-  s.shape64 = dslash_shape(g, HMC_F64);
+  s.shape64 = dslash_run_shape(g, HMC_F64);
   return c.off;
 }
 

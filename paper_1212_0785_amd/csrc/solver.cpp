@@ -618,8 +618,8 @@ hmc_status cg_solve_impl(Fields* F, void* x, const void* b, const hmc_cg_params*
   v.slot = F->slots + SL_SOLVER;
   v.state = F->state;
   // shapes fixed for the whole solve (the partial counts follow from them)
-  v.shape = dslash_shape(F->g, prec);
-  v.shape64 = dslash_shape(F->g, HMC_F64);
+  v.shape = dslash_run_shape(F->g, prec);
+  v.shape64 = dslash_run_shape(F->g, HMC_F64);
   v.nbD = dslash_shape_blocks(F->g.Vh, v.shape);
   v.nbR = F->nbR;
   hmc_cg_stats S{};

@@ -1,7 +1,7 @@
 // Launch-shape and link-form decisions and their persisted tuning table
 // (the auto-tuner of Sec. 4, for the choices this library offers): per
-// lattice and storage, the Dslash shape (one site per work-item, 2- or
-// 4-way direction split), its link streaming, site order and workgroups per
+// lattice and storage, the Dslash shape (one site per work-item, two
+// wavefronts per site, or one wavefront per hop), its link streaming, site order and workgroups per
 // CU, the staple-force shape (one link per work-item, plane split, or four
 // directions of 64 sites per block in the tiled walk), and
 // the compact link form of the hop and staple kernels (two rows, or row 0
@@ -152,7 +152,8 @@ int tune_save(const char* path) {
   if (!f) return -1;
   std::fprintf(f,
                "# kind L0 L1 L2 L3 prec choice us\n"
-               "# dslash: choice 1 = one site per work-item, 2|4 = direction split; us per CG iteration in a solve\n"
+               "# dslash: choice 1 = one site per work-item, 2 = two wavefronts per site, 4 = one wavefront per hop; us per "
+               "CG iteration in a solve\n"
                "# gauge_force: choice 0 = one link per work-item, 1 = plane split, 2 = four directions of 64 sites per "
                "block; us per launch\n"
                "# dslash_links, gauge_force_links: reals read per SU(3) link, 12 = two rows, 10 = row 0 and column 2\n"
@@ -189,19 +190,37 @@ int dslash_link_form(const LatArg& g, hmc_prec prec) {
   if (forced_link_form() > 0) return forced_link_form();
   const int t = tune_lookup(g.L, TUNE_DSLASH_LINKS, prec);
   if (t > 0) return t;
-  // measured on MI355X: the 10-real form's reconstruction lengthens each
-  // hop, which costs at 16^3x32 (latency-bound) and pays at 48^3x96
-  return g.Vh >= (1 << 20) ? LINK_ROWCOL : LINK_ROWS2;
+  // The 10-real form saves a sixth of the link bytes and adds ~40 operations
+  // and a division per link: it pays once the links' bytes count, later for
+  // the 2-byte storages, whose hop is bound by its instructions sooner.
+  // Measured (Mhat, two rows / row 0 + column 2, us): FP64 12^3x24 13.4 /
+  // 13.7, 16^3x32 30.8 / 29.7, 20^3x40 71.5 / 69.8; FP32 12^3x24 11.1 / 12.1,
+  // 16^3x32 17.8 / 17.4, 24^3x48 75 / 68; FP16 24^3x48 46 / 51, 32^3x64
+  // 155 / 149; BF16 24^3x48 42 / 45, 32^3x64 149 / 138
+  const int from = prec == HMC_F64 || prec == HMC_F32 ? 1 << 16 : 1 << 20;
+  return g.Vh >= from ? LINK_ROWCOL : LINK_ROWS2;
 }
+
+namespace {
+// Bytes of all links in the ten-real form at storage prec.
+double compact_link_bytes(const LatArg& g, hmc_prec prec) {
+  return 8.0 * g.Vh * (prec == HMC_F64 ? 80 : prec == HMC_F32 ? 40 : 20);
+}
+}  // namespace
 
 bool dslash_link_stream(const LatArg& g, hmc_prec prec) {
   static const int forced = env_int("HMC_LINK_STREAM");
   if (forced >= 0) return forced != 0;
   const int t = tune_lookup(g.L, TUNE_DSLASH_STREAM, prec);
   if (t >= 0) return t != 0;
-  // measured on MI355X: 17% faster FP64 Dslash at 48^3x96, 30% slower at
-  // 16^3x32, whose fields stay in the last-level cache between launches
-  return g.Vh >= (1 << 20);
+  // Streaming pays once the links a hop reads no longer stay in the 256 MB
+  // last-level cache from one hop to the next, beside the vectors; before
+  // that the hints only bypass it.  Measured (Mhat, plain / streamed, us, with
+  // the links' MB): FP64 20^3x40 (102 MB) 70 / 79, 24^3x48 (212) 161 / 157,
+  // 32^3x64 (671) 575 / 480; FP32 24^3x48 (106) 68 / 85, 32^3x64 (336) 288 /
+  // 260; BF16 32^3x64 (168) 138 / 145 on links just used, 149 / 146 on others
+  // and 575 / 572 per iteration of a solve, 40^3x80 (410) 356 / 324
+  return compact_link_bytes(g, prec) >= 150e6;
 }
 
 int dslash_tiled_order(const LatArg& g, hmc_prec prec) {
@@ -211,7 +230,11 @@ int dslash_tiled_order(const LatArg& g, hmc_prec prec) {
   if (forced >= 0) return forced == 0 ? 0 : tiled_order_valid(g, forced) ? forced : 1;
   const int t = tune_lookup(g.L, TUNE_DSLASH_ORDER, prec);
   if (t >= 0) return t == 0 ? 0 : tiled_order_valid(g, t) ? t : 1;
-  return 0;
+  // whole z-planes for FP64 once a t-slice outgrows an XCD's L2 (linear /
+  // tiled with two blocks per CU, Mhat: 32^3x64 507 / 493 us, 40^3x80 1349 /
+  // 1274 us); the narrower storages gain nothing from it (40^3x80 FP32 698 /
+  // 739, BF16 324 / 548 us)
+  return prec == HMC_F64 && g.Vh >= (1 << 20) ? 1 : 0;
 }
 
 int dslash_tiled_occupancy(const LatArg& g, hmc_prec prec) {
@@ -238,9 +261,19 @@ int dslash_shape(const LatArg& g, hmc_prec prec) {
   if (forced > 0) return forced;
   const int t = tune_lookup(g.L, TUNE_DSLASH, prec);
   if (t > 0) return t;
-  // measured on MI355X: the 4-way split gains for FP32 arithmetic up to
-  // 16^3x32 and loses at 48^3x96; FP64 is even at 16^3x32
-  return (prec != HMC_F64 && g.Vh <= (1 << 17)) ? 4 : 1;
+  // One wavefront per hop while the latency of a hop's loads counts, one site
+  // per work-item once the launch fills the chip many times over; FP64 between
+  // them in two wavefronts per site (measured, Mhat in us, 1 / 2 / 4:
+  // 16^3x32 FP64 34.6 / 31.1 / 29.7, FP32 21.3 / 19.3 / 17.4, BF16 15.9 / 14.7
+  // / 12.4; 24^3x48 FP64 182 / 159 / 157, FP32 88 / 74 / 68, BF16 43.9 / 42.1
+  // / 40.7; 32^3x64 FP64 507 / 479 / 478, FP32 261 / 260 / 254, BF16 138 / 148
+  // / 151; in a solve, where the split shapes' norms have four times the
+  // partial sums, us per iteration: 24^3x48 FP32 291 / 271 / 270, FP16 203 /
+  // 206 / 215, BF16 186 / 193 / 196; 32^3x64 FP64 1243 / 1222 / 1257, FP32 844
+  // / 894 / 887; 40^3x80 FP64 Mhat, tiled / 2: 1274 / 1328)
+  // (below one block the choice has no effect: dslash_run_shape)
+  if (prec == HMC_F64) return g.Vh < kThreads ? 1 : g.Vh < (1 << 19) ? 4 : g.Vh < 3 << 19 ? 2 : 1;
+  return g.Vh < (prec == HMC_F32 ? 1 << 19 : 1 << 18) ? 4 : 1;
 }
 
 bool exp_update_stream(const LatArg& g) {
