@@ -329,14 +329,19 @@ hipError_t ensure_lowprec(Fields* F, hmc_prec prec, hipStream_t st) {
 // loads are taken to reproduce the link (links have entries of modulus <= 1).
 constexpr double kSu3Tol = 1e-14;
 
-hipError_t check_su3(Fields* F, hipStream_t st) {
-  hipError_t e = launch_su3_check(F->g, F->U, kSu3Tol, F->part[4], F->nbR, st);
+// Sets F->su3 from the n per-block counts of links that are not SU(3) (syncs).
+static hipError_t read_su3(Fields* F, int n, hipStream_t st) {
+  hipError_t e = launch_finalize(F->part[4], n, 1, F->slots + SL_RED, 1.0, 0, st);
   if (e != hipSuccess) return e;
-  if ((e = launch_finalize(F->part[4], F->nbR, 1, F->slots + SL_RED, 1.0, 0, st))) return e;
   double bad = -1;
   if ((e = read_slots(F, SL_RED, 1, &bad, st))) return e;
   F->su3 = bad == 0.0;
   return hipSuccess;
+}
+
+hipError_t check_su3(Fields* F, hipStream_t st) {
+  hipError_t e = launch_su3_check(F->g, F->U, kSu3Tol, F->part[4], F->nbR, st);
+  return e != hipSuccess ? e : read_su3(F, F->nbR, st);
 }
 
 // Mhat (dag) on F64 half spinors: out = in - kappa^2 D_eo D_oe in.
@@ -531,9 +536,9 @@ hmc_status hmc_links_two_row(hmc_fields* f, int32_t* on) {
 hmc_status hmc_import_gauge(hmc_fields* f, const void* canon, void* stream) {
   FIELDS(f);
   HMC_REQUIRE(canon, "null buffer");
-  HMC_CHECK_HIP(launch_pack_gauge(F->g, canon, F->U, ST(stream)));
+  HMC_CHECK_HIP(launch_pack_gauge(F->g, canon, F->U, kSu3Tol, F->part[4], ST(stream)));
   F->u_version++;
-  HMC_CHECK_HIP(check_su3(F, ST(stream)));
+  HMC_CHECK_HIP(read_su3(F, pack_gauge_blocks(F->g.Vh), ST(stream)));
   return HMC_OK;
 }
 
@@ -720,13 +725,16 @@ hmc_status hmc_sum_multi(hmc_fields* f, const void* x, int32_t nhalves, const in
   HMC_REQUIRE(nsub >= 1 && nsub <= 1024, "nsub must be in [1, 1024]");
   hipStream_t st = ST(stream);
   const int nb = std::min(F->nbR, 1024);
-  std::vector<double> host(nsub);
   // rows of partials first, the nsub results in the last 1024 doubles
   double* res = F->multi + F->multi_doubles - 1024;
   HMC_CHECK_HIP(launch_sum_multi(F->g, x, nhalves, subset, nsub, F->multi, nb, res, st));
-  HMC_CHECK_HIP(hipMemcpyAsync(host.data(), res, nsub * sizeof(double), hipMemcpyDeviceToHost, st));
+  // through the pinned buffer where it holds them (a copy to pageable memory
+  // is staged by the runtime)
+  std::vector<double> host(nsub > SL_COUNT ? nsub : 0);
+  double* to = nsub > SL_COUNT ? host.data() : F->pinned;
+  HMC_CHECK_HIP(hipMemcpyAsync(to, res, nsub * sizeof(double), hipMemcpyDeviceToHost, st));
   HMC_CHECK_HIP(hipStreamSynchronize(st));
-  for (int k = 0; k < nsub; ++k) out[k] = host[k];
+  for (int k = 0; k < nsub; ++k) out[k] = to[k];
   return HMC_OK;
 }
 

@@ -167,7 +167,10 @@ hipError_t launch_dslash(hmc_prec prec, int dagger, int epi, const LatArg& g, in
                          int nbatch, const DslashArgs& one, hipStream_t st, int j = 0);
 
 // Layout conversion between canonical AoS complex128 (device) and SoA.
-hipError_t launch_pack_gauge(const LatArg& g, const void* canon, void* U, hipStream_t st);
+// (the links' import also counts those that are not SU(3) to `tol`, one count
+// per block into bad[0 .. pack_gauge_blocks))
+int pack_gauge_blocks(int Vh);
+hipError_t launch_pack_gauge(const LatArg& g, const void* canon, void* U, double tol, double* bad, hipStream_t st);
 hipError_t launch_unpack_gauge(const LatArg& g, const void* U, void* canon, hipStream_t st);
 hipError_t launch_pack_spinor(const LatArg& g, const void* canon, void* half, int par, hipStream_t st);
 hipError_t launch_unpack_spinor(const LatArg& g, const void* half, void* canon, int par, hipStream_t st);
