@@ -102,9 +102,7 @@ __global__ void __launch_bounds__(kBlock) k_sum_multi_partials(Lat g, const void
     while (left) {
       const int id = __shfl(sub, __ffsll((long long)left) - 1, 64);
       const bool in = sub == id;
-      double t = in ? v : 0.0;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
+      const double t = wave_sum(in ? v : 0.0);
       if (lane == 0) mine[id] += t;
       left &= ~__ballot(in);
     }
@@ -219,17 +217,18 @@ __device__ __forceinline__ const CgArgs& cg_args(const CgArgs* table, const CgAr
 }
 
 // One solver iteration with label k = iter0 + j; cur = k & 1, nxt = cur ^ 1.
-//   update:  alpha = sum(pp[cur]) / sum(pq);  x += alpha p;  r -= alpha q;
-//            per-block |r|^2 -> pp[nxt] (CG) or pr (CGLS)
-//   pupdate: beta = sum(pp[nxt]) / sum(pp[cur]);  p = src + beta p with
-//            src = r (CG) or s (CGLS); convergence measure |r|^2 =
-//            sum(pp[nxt]) (CG) or sum(pr) (CGLS).
+//   update (CGLS): alpha = sum(pp[cur]) / sum(pq) (block 0: into the solver
+//            state);  r -= alpha q;  per-block |r|^2 -> pr
+//   pupdate: beta = sum(pp[nxt]) / sum(pp[cur]);  x += alpha p;  p = src +
+//            beta p with src = r (CG) or s (CGLS); convergence measure
+//            |r|^2 = sum(pp[nxt]) (CG) or sum(pr) (CGLS).
 // (CG: pp holds |r|^2, pq = <p, A p> = |Mhat p|^2.  CGLS: pp holds
 // |s|^2 = |Mhat^dag r|^2, pq = |q|^2 = |Mhat p|^2.)
-// Fused CG (CgArgs::fused): the update kernel is not launched; the
-// preceding Dslash computes alpha (block 0, into the solver state) and
-// r -= alpha q in its epilogue, and the p-update also does x += alpha p.
-template <class SP, class SX, bool BATCH>
+// CG launches no update: its third Dslash computes alpha (block 0, into the
+// solver state) and the fourth does r -= alpha q in its epilogue.  x is left
+// to the p-update in both, which reads p anyway: with x in the CGLS update p
+// was read twice (24^3x48, FP64: update 67 -> 34 us, p-update 39 -> 54).
+template <class SP, bool BATCH>
 __global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table, CgArgs one, int j) {
   const CgArgs& a = cg_args<BATCH>(table, one);
   const int k = a.iter0 + a.state->base + j;
@@ -241,29 +240,23 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table
   double sums[2];
   sum_partials_n<kBlock / 64, 2>(part, n, sums);
   const double alpha = sums[0] / sums[1];
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.state->alpha = alpha;
   const R al = (R)alpha;
   double v[1] = {0.0};
   for (int s = blockIdx.x * kBlock + threadIdx.x; s < g.Vh; s += gridDim.x * kBlock) {
-    cx<R> p[12], q[12], r[12];
-    cx<typename SX::R> x[12];
-    SP::load(a.p, g.stride, s, p);
+    cx<R> q[12], r[12];
     SP::load(a.q, g.stride, s, q);
     SP::load(a.r, g.stride, s, r);
-    SX::load(a.x, g.stride, s, x);
 #pragma unroll
     for (int m = 0; m < 12; ++m) {
-      x[m].re = fma((typename SX::R)alpha, (typename SX::R)p[m].re, x[m].re);
-      x[m].im = fma((typename SX::R)alpha, (typename SX::R)p[m].im, x[m].im);
       r[m].re = fma(-al, q[m].re, r[m].re);
       r[m].im = fma(-al, q[m].im, r[m].im);
       v[0] += (double)r[m].re * r[m].re + (double)r[m].im * r[m].im;
     }
-    SX::store(a.x, g.stride, s, x);
     SP::store(a.r, g.stride, s, r);
   }
   block_sum<1>(v);
-  double* out = a.cgls ? a.pr : a.pp[cur ^ 1];
-  if (threadIdx.x == 0) out[blockIdx.x] = v[0];
+  if (threadIdx.x == 0) a.pr[blockIdx.x] = v[0];
 }
 
 // Block 0 records the iteration and, when |r|^2 <= thr (or, in mixed
@@ -302,14 +295,13 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
     const int s = lo + i - part * nsx;
     if constexpr (NP == 1) {
       SP::load(a.p, g.stride, s, p);
-      if (a.fused) SX::load(a.x, g.stride, s, x);
+      SX::load(a.x, g.stride, s, x);
       SP::load(src, g.stride, s, q);
     } else {
 #pragma unroll
       for (int c = 0; c < NC; ++c) p[c] = SP::load_one(a.p, g.stride, s, NC * part + c);
-      if (a.fused)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) x[c] = SX::load_one(a.x, g.stride, s, NC * part + c);
+      for (int c = 0; c < NC; ++c) x[c] = SX::load_one(a.x, g.stride, s, NC * part + c);
 #pragma unroll
       for (int c = 0; c < NC; ++c) q[c] = SP::load_one(src, g.stride, s, NC * part + c);
     }
@@ -318,8 +310,11 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
   // reduction, their latency overlaps it.
   const int i0 = (blockIdx.x >> 3) * kBlock + threadIdx.x;
   if (i0 < nwork) load(i0);
-  // the three sums of this step in one block reduction (same order, hence
-  // the same bits, in every block)
+  // the sums of this step in one block reduction (same order, hence the same
+  // bits, in every block).  sum(pp[cur]) is the previous iteration's
+  // sum(pp[nxt]), which its block 0 left in the state: it is summed again only
+  // by the first iteration after a start or restart.  (The state keeps both
+  // parities, so no block reads what this launch writes.)
   __shared__ double bc[3];
   __shared__ int fold_sh;
   {
@@ -327,16 +322,22 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
     // eight of them are issued together
     constexpr int U = 8;
     double v[3] = {0.0, 0.0, 0.0};
+    const bool restarted = k == stt->ru_label;
     for (int base = threadIdx.x; base < a.n_pp; base += U * kBlock) {
-      double t0[U], t1[U];
+      double t0[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = base + u * kBlock;
         t0[u] = i < a.n_pp ? a.pp[nxt][i] : 0.0;
-        t1[u] = i < a.n_pp ? a.pp[cur][i] : 0.0;
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[0] += t0[u], v[1] += t1[u];
+      for (int u = 0; u < U; ++u) v[0] += t0[u];
+      if (restarted)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = base + u * kBlock;
+          v[1] += i < a.n_pp ? a.pp[cur][i] : 0.0;
+        }
     }
     if (a.cgls)
       for (int base = threadIdx.x; base < a.n_pr; base += U * kBlock) {
@@ -351,7 +352,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
       }
     block_sum<3>(v);
     if (threadIdx.x == 0) {
-      bc[0] = v[0], bc[1] = v[1], bc[2] = v[2];
+      bc[0] = v[0], bc[1] = restarted ? v[1] : stt->sum_pp[cur], bc[2] = v[2];
       // mixed precision with device-driven updates: does this iteration ask
       // for one?  (Block 0 may already have raised maxrr to max(maxrr, rr):
       // every block gets the same answer.)
@@ -367,7 +368,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
   const double nw = bc[0], old = bc[1];
   const double rr = a.cgls ? bc[2] : nw;
   const bool conv = rr <= stt->thr;
-  const double alpha = a.fused ? stt->alpha : 0.0;
+  const double alpha = stt->alpha;
   // the iteration that asks for an update folds the inner solution into
   // the FP64 one (x64 += xl, xl = 0) for the update that follows
   const bool fold = fold_sh != 0;
@@ -375,6 +376,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
     stt->iters += 1;
     stt->last = k;
     stt->rr = rr;
+    stt->sum_pp[nxt] = nw;
     if (a.mixed) {
       double mx = fmax(stt->maxrr, rr);
       stt->maxrr = mx;
@@ -393,24 +395,16 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
     }
   }
   const bool p_done = conv && !a.mixed;  // converged: the search direction is not needed
-  if (p_done && !a.fused) return;
   const R beta = (R)(nw / old);
   for (int i = i0; i < nwork; i += nbx * kBlock) {
     const int part = NP == 1 ? 0 : i / nsx;
     const int s = lo + i - part * nsx;
     if (i != i0) load(i);
-    if (a.fused) {  // x += alpha p with the p of this iteration
+    // x += alpha p with the p of this iteration
 #pragma unroll
-      for (int m = 0; m < NC; ++m) {
-        x[m].re = fma((XR)alpha, (XR)p[m].re, x[m].re);
-        x[m].im = fma((XR)alpha, (XR)p[m].im, x[m].im);
-      }
-    } else if (fold) {  // CGLS: x was updated by the update kernel
-      if constexpr (NP == 1)
-        SX::load(a.x, g.stride, s, x);
-      else
-#pragma unroll
-        for (int c = 0; c < NC; ++c) x[c] = SX::load_one(a.x, g.stride, s, NC * part + c);
+    for (int m = 0; m < NC; ++m) {
+      x[m].re = fma((XR)alpha, (XR)p[m].re, x[m].re);
+      x[m].im = fma((XR)alpha, (XR)p[m].im, x[m].im);
     }
     if (fold) {
 #pragma unroll
@@ -421,12 +415,10 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
         x[m] = {(XR)0, (XR)0};
       }
     }
-    if (a.fused || fold) {
-      if constexpr (NP == 1)
-        SX::store(a.x, g.stride, s, x);
-      else
-        SX::store_part(a.x, g.stride, s, part, x);
-    }
+    if constexpr (NP == 1)
+      SX::store(a.x, g.stride, s, x);
+    else
+      SX::store_part(a.x, g.stride, s, part, x);
     if (p_done) continue;
 #pragma unroll
     for (int m = 0; m < NC; ++m) {
@@ -466,12 +458,6 @@ __global__ void k_state_reset(SolverState* st, const double* maxrr, int nbatch, 
   if (label >= 0) st[k].ru_label = label;
 }
 
-// dst = src over n doubles while *gate != 0.
-__global__ void k_copy_doubles_gated(double* dst, const double* src, int n, const int* gate) {
-  if (*gate == 0) return;
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) dst[i] = src[i];
-}
-
 __global__ void k_advance_base(SolverState* st, int n) {
   if (threadIdx.x == 0) st->base += n;
 }
@@ -486,9 +472,9 @@ __global__ void k_ru_request(SolverState* st) {
 // block; every thread reads the gate before thread 0 clears it (the sum
 // synchronises the block in between).
 __global__ void __launch_bounds__(kBlock) k_ru_finish(SolverState* st, const double* part64, int n, double* slot,
-                                                     int max_ru, int max_iters) {
+                                                     int advance, int max_ru, int max_iters) {
   if (st->ru_gate == 0) {
-    if (threadIdx.x == 0) st->restart = 0;
+    if (threadIdx.x == 0) st->restart = 0, st->base += advance;
     return;
   }
   const double rr64 = sum_partials(part64, n);
@@ -502,6 +488,7 @@ __global__ void __launch_bounds__(kBlock) k_ru_finish(SolverState* st, const dou
   // iteration diverge: p restarts from the new residual instead.
   st->restart = rr64 > 2.0 * st->rr || (st->nru > 0 && rr64 >= st->rr64);
   st->nru += 1;
+  st->base += advance;
   st->ru_iter = st->iters;
   st->ru_label = st->base;
   st->rr64 = rr64;
@@ -700,8 +687,8 @@ static double cg_vec_bytes(hmc_prec prec, bool with_x, int nsp) {
 
 hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, int nb, const CgArgs* table,
                             int nbatch, int j, hipStream_t st) {
-  // x += alpha p, r -= alpha q: x read + written, p and q read, r read + written
-  TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, true, 4) * g.Vh * nbatch);
+  // r -= alpha q: q read, r read + written
+  TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, false, 3) * g.Vh * nbatch);
   const dim3 grid(nb, nbatch), block(kBlock);
   auto go = [&](auto kernel_single, auto kernel_batch) {
     if (table)
@@ -710,18 +697,18 @@ hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, int
       hipLaunchKernelGGL(kernel_single, grid, block, 0, st, to_lat(g), table, a, j);
   };
   switch (prec) {
-    case HMC_F64: go(k_cg_update<SpF64, SpF64, false>, k_cg_update<SpF64, SpF64, true>); break;
-    case HMC_F32: go(k_cg_update<SpF32, SpF32, false>, k_cg_update<SpF32, SpF32, true>); break;
-    case HMC_F16: go(k_cg_update<SpF16, SpF32, false>, k_cg_update<SpF16, SpF32, true>); break;
-    case HMC_BF16: go(k_cg_update<SpBF16, SpF32, false>, k_cg_update<SpBF16, SpF32, true>); break;
+    case HMC_F64: go(k_cg_update<SpF64, false>, k_cg_update<SpF64, true>); break;
+    case HMC_F32: go(k_cg_update<SpF32, false>, k_cg_update<SpF32, true>); break;
+    case HMC_F16: go(k_cg_update<SpF16, false>, k_cg_update<SpF16, true>); break;
+    case HMC_BF16: go(k_cg_update<SpBF16, false>, k_cg_update<SpBF16, true>); break;
   }
   return hipGetLastError();
 }
 
 hipError_t launch_cg_pupdate(const LatArg& g, hmc_prec prec, const CgArgs& a, int nb, const CgArgs* table,
                              int nbatch, int j, hipStream_t st) {
-  // p = r + beta p: p read + written, r read (fused: x += alpha p as well)
-  TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, a.fused != 0, 3) * g.Vh * nbatch);
+  // x += alpha p, p = r + beta p: x and p read + written, r read
+  TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, true, 3) * g.Vh * nbatch);
   (void)nb;  // the update writes no partial sums: its grid is its own
   // multiples of 8 blocks (one share per XCD)
   const int nb4 = std::min(8 * ceil_div(4LL * g.Vh, 8 * kBlock), 2048);
@@ -755,20 +742,15 @@ hipError_t launch_advance_base(SolverState* st_dev, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_copy_doubles_gated(double* dst, const double* src, int n, const int* gate, hipStream_t st) {
-  hipLaunchKernelGGL(k_copy_doubles_gated, dim3(std::max(1, std::min(ceil_div(n, kBlock), 64))), dim3(kBlock), 0, st,
-                     dst, src, n, gate);
-  return hipGetLastError();
-}
-
 hipError_t launch_ru_request(SolverState* st_dev, hipStream_t st) {
   hipLaunchKernelGGL(k_ru_request, dim3(1), dim3(64), 0, st, st_dev);
   return hipGetLastError();
 }
 
-hipError_t launch_ru_finish(SolverState* st_dev, const double* part64, int n, double* rr64_slot, int max_ru,
-                            int max_iters, hipStream_t st) {
-  hipLaunchKernelGGL(k_ru_finish, dim3(1), dim3(kBlock), 0, st, st_dev, part64, n, rr64_slot, max_ru, max_iters);
+hipError_t launch_ru_finish(SolverState* st_dev, const double* part64, int n, double* rr64_slot, int advance,
+                            int max_ru, int max_iters, hipStream_t st) {
+  hipLaunchKernelGGL(k_ru_finish, dim3(1), dim3(kBlock), 0, st, st_dev, part64, n, rr64_slot, advance, max_ru,
+                     max_iters);
   return hipGetLastError();
 }
 

@@ -971,16 +971,51 @@ __device__ __forceinline__ void box_muller(uint64_t w0, uint64_t w1, double* g0,
 
 // ------------------------------------------------------------ reductions
 
-// Deterministic sum over the block: wave64 butterfly (fixed xor order),
-// then wave partials combined by thread 0 in wave order.  Result valid in
-// thread 0 only.  `N` values reduced at once; W wavefronts per block.
+// v moved between lanes by a DPP control (within rows of 16 lanes).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const uint64_t u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// Sum over the wavefront in the order of an xor butterfly (distances 32, 16,
+// 8, 4, 2, 1), the same in every lane, without a trip through LDS per step (six
+// of them were ~0.4 us of each kernel that ends in a sum).  Halves and rows
+// are exchanged by the lane-swap instructions: of v and a copy of it, one
+// result holds the lower half (even row) twice and the other the upper (odd)
+// one.  Within a row the partner at distance 8 is a rotation by 8; after that
+// step the values repeat every 8 lanes, so a rotation by 4 meets the partner
+// at distance 4; the last two steps permute quads.
+__device__ __forceinline__ double wave_sum(double v) {
+  typedef unsigned pair __attribute__((ext_vector_type(2)));
+#define HMC_SWAP_ADD(SWAP)                                                                   \
+  do {                                                                                       \
+    const uint64_t u = __double_as_longlong(v);                                              \
+    const unsigned l = (unsigned)u, h = (unsigned)(u >> 32);                                 \
+    const pair a = __builtin_bit_cast(pair, SWAP(l, l, false, false));                       \
+    const pair b = __builtin_bit_cast(pair, SWAP(h, h, false, false));                       \
+    v = __longlong_as_double(((uint64_t)b.x << 32) | a.x) + __longlong_as_double(((uint64_t)b.y << 32) | a.y); \
+  } while (0)
+  HMC_SWAP_ADD(__builtin_amdgcn_permlane32_swap);
+  HMC_SWAP_ADD(__builtin_amdgcn_permlane16_swap);
+#undef HMC_SWAP_ADD
+  v += dpp_move<0x128>(v);  // row_ror:8
+  v += dpp_move<0x124>(v);  // row_ror:4
+  v += dpp_move<0x4e>(v);   // quad_perm:[2,3,0,1]
+  v += dpp_move<0xb1>(v);   // quad_perm:[1,0,3,2]
+  return v;
+}
+
+// Deterministic sum over the block: wave_sum, then the wavefronts' sums
+// combined by thread 0 in wave order.  Result valid in thread 0 only.  `N`
+// values reduced at once; W wavefronts per block.  Every work-item takes part.
 template <int N, int W = kBlock / 64>
 __device__ __forceinline__ void block_sum(double* v) {
   __shared__ double red[N][W];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-    for (int k = 0; k < N; ++k) v[k] += __shfl_xor(v[k], off, 64);
+  for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0)
 #pragma unroll

@@ -103,6 +103,13 @@ __device__ __forceinline__ void alpha_prologue(const DslashArgs& e, int label) {
   if (threadIdx.x == 0) *(HMC_GLOBAL double*)e.alpha_out = s[0] / s[1];
 }
 
+// The block's |out|^2 (thread 0's v) into its partial-sum slot or slots.
+__device__ __forceinline__ void put_partial(const DslashArgs& e, int label, int b, double v) {
+  if (threadIdx.x != 0) return;
+  if (e.partial) ((HMC_GLOBAL double*)e.partial)[b] = v;
+  if (e.partial_pp[0]) ((HMC_GLOBAL double*)e.partial_pp[e.partial ? 0 : (label + 1) & 1])[b] = v;
+}
+
 // BATCH: blockIdx.y selects an entry of `table` (same-volume requests share
 // one launch); otherwise the single entry `one` is read from the kernel
 // arguments.
@@ -158,8 +165,7 @@ __global__ void __launch_bounds__(kBlock) HMC_DSLASH_WAVES k_dslash(Lat g, int o
   }
   if (EPI == EPI_AXPY_NORM || EPI == EPI_CG) {
     block_sum<1>(nrm);
-    double* dst = e.partial_pp[0] ? e.partial_pp[(label + 1) & 1] : e.partial;
-    if (threadIdx.x == 0) ((HMC_GLOBAL double*)dst)[b] = nrm[0];
+    put_partial(e, label, b, nrm[0]);
   }
 }
 
@@ -260,8 +266,7 @@ __global__ void __launch_bounds__(128) k_dslash_split(Lat g, int out_par, const 
   }
   if (EPI == EPI_AXPY_NORM || EPI == EPI_CG) {
     block_sum<1, 2>(nrm);
-    double* dst = e.partial_pp[0] ? e.partial_pp[(label + 1) & 1] : e.partial;
-    if (threadIdx.x == 0) ((HMC_GLOBAL double*)dst)[b] = nrm[0];
+    put_partial(e, label, b, nrm[0]);
   }
 }
 
@@ -440,8 +445,7 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
   }
   if (EPI == EPI_AXPY_NORM || EPI == EPI_CG) {
     block_sum<1, 8>(nrm);
-    double* dst = e.partial_pp[0] ? e.partial_pp[(label + 1) & 1] : e.partial;
-    if (threadIdx.x == 0) ((HMC_GLOBAL double*)dst)[b] = nrm[0];
+    put_partial(e, label, b, nrm[0]);
   }
 }
 

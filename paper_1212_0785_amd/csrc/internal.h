@@ -125,6 +125,7 @@ struct SolverState {
   double alpha;  // CG step length of the current iteration (fused form)
   double thr;    // stop threshold on |r|^2 (< 0: never)
   double rr64;   // FP64 |r|^2 of the last device-driven reliable update
+  double sum_pp[2];  // sum of the ping-pong partials, by label parity (from the second iteration after a restart)
 };
 
 // Iteration labels: a solver iteration carries the label iter0 + base + j,
@@ -142,7 +143,7 @@ struct DslashArgs {
   const void* y;        // epilogue addend on the output parity (may be null)
   double a, b;          // out = a*y + b*(D in) for the AXPY epilogues
   double* partial;      // per-block |out|^2 for the NORM epilogue
-  double* partial_pp[2];  // if set: partial_pp[(label + 1) & 1] instead
+  double* partial_pp[2];  // if set: partial_pp[(label + 1) & 1] instead; partial_pp[0] as well where both are set
   const int* stop_at;   // solver control (may be null)
   const int* label_base;  // added to the label when set (the solver state's base)
   int iter0;            // label offset compared with *stop_at
@@ -226,7 +227,6 @@ struct CgArgs {
   void* x64;       // mixed precision with device-driven updates: the FP64 solution, into which the
                    // iteration that asks for an update folds the inner solution (null: the host does)
   int mixed;       // 1: never declare convergence, pause instead
-  int fused;       // CG with the residual update in the Dslash epilogue: the p-update also does x += alpha p
   int max_iters;   // device-driven updates: the iteration that completes this many asks for the last one (0: none)
 };
 hipError_t launch_cg_init(const LatArg& g, hmc_prec prec, const void* b, void* x, void* r, void* p, double* part,
@@ -251,20 +251,19 @@ hipError_t launch_add_low_to_f64(const LatArg& g, void* x64, void* xlow, hipStre
 // |r64|^2 partials into *rr64_slot, counts the update and either ends the
 // solve (converged, non-finite, max_ru updates or max_iters iterations
 // reached) or resumes the inner iteration (stop_at = INT_MAX, maxrr =
-// |r64|^2); sets st->restart when the search direction must restart (the
+// |r64|^2) after advancing the label base by `advance` (with or without an
+// update pending); sets st->restart when the search direction must restart (the
 // FP64 residual exceeds twice the inner one that asked for the update, or
 // did not fall below the previous update's), else clears it (also when no
 // update was pending); clears the gate.
-hipError_t launch_ru_finish(SolverState* st_dev, const double* part64, int n, double* rr64_slot, int max_ru,
-                            int max_iters, hipStream_t st);
+hipError_t launch_ru_finish(SolverState* st_dev, const double* part64, int n, double* rr64_slot, int advance,
+                            int max_ru, int max_iters, hipStream_t st);
 // Device-driven reliable update after q = A x (gated): r64 = rhs - q with
 // |r64|^2 partials (nb blocks), r = r64 in storage prec; with pp0 set also
 // the |r|^2 partials of the stored r into pp0 and pp1 (nb = the iteration's
 // partial count).
 hipError_t launch_ru_residual(const LatArg& g, hmc_prec prec, const void* rhs, const void* q, void* r64, void* rlow,
                               double* part64, double* pp0, double* pp1, int nb, const int* gate, hipStream_t st);
-// dst = src over n doubles while *gate != 0.
-hipError_t launch_copy_doubles_gated(double* dst, const double* src, int n, const int* gate, hipStream_t st);
 // Asks for a reliable update from the host: opens the gate and stops the
 // iterations still queued.
 hipError_t launch_ru_request(SolverState* st_dev, hipStream_t st);

@@ -101,7 +101,6 @@ void build_iteration(const SolveVecs& v, int iter0, int mixed, double delta2, It
   c.delta2 = delta2;
   c.x64 = mixed && device_updates ? v.x : nullptr;
   c.mixed = mixed;
-  c.fused = v.cgls ? 0 : 1;
   o->c[0] = c;
   o->c[1] = c;
 }
@@ -183,9 +182,10 @@ hipError_t reliable_update(const SolveVecs& v, hipStream_t st) {
 }
 
 // r = low(r64) (unless already converted) and the inner |r|^2 (CG) or
-// s = Mhat^dag r with |s|^2 (CGLS) into `part`, optionally gated.
+// s = Mhat^dag r with |s|^2 (CGLS) into `part` (CGLS: and part2 if set),
+// optionally gated.
 static hipError_t restart_vectors(const SolveVecs& v, double* part, hipStream_t st, const int* gate,
-                                  bool convert = true) {
+                                  bool convert = true, double* part2 = nullptr) {
   hipError_t e;
   if (convert && (e = launch_convert_spinor(v.g, v.r64, HMC_F64, v.r, v.prec, 1, nullptr, nullptr, st, gate)))
     return e;
@@ -205,6 +205,7 @@ static hipError_t restart_vectors(const SolveVecs& v, double* part, hipStream_t 
   d.y = v.r;
   d.b = -v.kappa * v.kappa;
   d.partial = part;
+  d.partial_pp[0] = part2;
   return launch_dslash(v.prec, 1, EPI_AXPY_NORM, v.g, 0, nullptr, 1, d, st, 0);
 }
 
@@ -228,22 +229,21 @@ hipError_t inner_restart(const SolveVecs& v, int k, bool first, hipStream_t st, 
 // the next iteration finds it whatever the parity of its label; the other
 // buffer is rewritten before it is read), then the decision, and p = r
 // (CG) or s (CGLS) where the decision restarts the search direction.
-static hipError_t reliable_update_block(const SolveVecs& v, int max_ru, int max_iters, hipStream_t st) {
+static hipError_t reliable_update_block(const SolveVecs& v, int advance, int max_ru, int max_iters, hipStream_t st) {
   const int* gate = &v.state->ru_gate;
   hipError_t e;
   if (v.cgls) {
     if ((e = mhat64_gated(v, v.q64, v.x, 0, nullptr, st, gate))) return e;
     if ((e = launch_ru_residual(v.g, v.prec, v.rhs, v.q64, v.r64, v.r, v.red, nullptr, nullptr, v.nbD, gate, st)))
       return e;
-    if ((e = restart_vectors(v, v.pp[0], st, gate, false))) return e;
-    if ((e = launch_copy_doubles_gated(v.pp[1], v.pp[0], v.nbD, gate, st))) return e;
+    if ((e = restart_vectors(v, v.pp[0], st, gate, false, v.pp[1]))) return e;
   } else {
     if ((e = mhat64_gated(v, v.s64, v.x, 0, nullptr, st, gate))) return e;
     if ((e = mhat64_gated(v, v.q64, v.s64, 1, nullptr, st, gate))) return e;
     if ((e = launch_ru_residual(v.g, v.prec, v.rhs, v.q64, v.r64, v.r, v.red, v.pp[0], v.pp[1], v.nbD, gate, st)))
       return e;
   }
-  if ((e = launch_ru_finish(v.state, v.red, v.nbD, v.slot, max_ru, max_iters, st))) return e;
+  if ((e = launch_ru_finish(v.state, v.red, v.nbD, v.slot, advance, max_ru, max_iters, st))) return e;
   return launch_copy_gated(v.p, v.cgls ? v.s : v.r, low_half_bytes(v), &v.state->restart, st);
 }
 
@@ -270,9 +270,8 @@ hipError_t chunk_launches(const SolveVecs& v, const IterArgs& args, int n, const
     hipError_t e = launch_iteration(v.g, v.prec, v.cgls, nullptr, args, 1, v.nbD, v.nbR, j, st);
     if (e != hipSuccess) return e;
   }
-  hipError_t e = launch_advance_base(v.state, n, st);
-  if (e != hipSuccess || !x.ru) return e;
-  return reliable_update_block(v, x.max_ru, x.max_iters, st);
+  // the update's last kernel advances the label base itself
+  return x.ru ? reliable_update_block(v, n, x.max_ru, x.max_iters, st) : launch_advance_base(v.state, n, st);
 }
 
 // Which chunks are replayed from recordings.  Measured on MI355X (ROCm
@@ -559,7 +558,7 @@ hipError_t run_mixed(Fields* F, const SolveVecs& v, const IterArgs& args, int li
       // which ends the solve (max_iters 0: converged or at the limit)
       if ((e = launch_ru_request(v.state, st))) return e;
       if ((e = launch_add_low_to_f64(v.g, v.x, v.xl, st))) return e;
-      if ((e = reliable_update_block(v, x.max_ru, 0, st))) return e;
+      if ((e = reliable_update_block(v, 0, x.max_ru, 0, st))) return e;
       return read_state(F, stt, st);
     }
     cur = Chunk{labels, queued, cur.slot ^ 1};
