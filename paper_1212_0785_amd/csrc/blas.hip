@@ -228,14 +228,96 @@ __device__ __forceinline__ const CgArgs& cg_args(const CgArgs* table, const CgAr
 // solver state) and the fourth does r -= alpha q in its epilogue.  x is left
 // to the p-update in both, which reads p anyway: with x in the CGLS update p
 // was read twice (24^3x48, FP64: update 67 -> 34 us, p-update 39 -> 54).
+//
+// Four work-items share a site in both kernels: work-item (part, s) updates the
+// components 3 part .. 3 part + 2 of site s.  For a storage with a per-site
+// scale, which needs all twelve components, the four are the wavefronts of one
+// block, which exchange their largest components through LDS.  XCD x (hardware blocks b with b % 8 == x;
+// gridDim.x is a multiple of 8) takes the sites [x Vh / 8, (x + 1) Vh / 8),
+// the range the Dslash's XCD-aware block order gives the same XCD, so the
+// vectors stay in the L2 of the XCD that reads them next.  The first element's
+// loads depend on no sum and are issued before anything is waited for.
+struct VecRange {
+  int lo, nsx, nwork, first, step;
+};
+// Element i of a range is part i / nsx of site lo + i % nsx; SCALED: wavefront
+// w of a block has part w of 64 sites, so i runs over groups of 64 sites times
+// four parts, and all four wavefronts of a block make the same steps.
+template <bool SCALED>
+__device__ __forceinline__ VecRange vec_range(const Lat& g) {
+  VecRange v;
+  const int xcd = blockIdx.x & 7, nbx = gridDim.x >> 3;
+  v.lo = (int)((long long)g.Vh * xcd / 8);
+  v.nsx = (int)((long long)g.Vh * (xcd + 1) / 8) - v.lo;
+  v.nwork = SCALED ? (v.nsx + 63) / 64 * kBlock : v.nsx * 4;
+  v.first = (blockIdx.x >> 3) * kBlock + threadIdx.x;
+  v.step = nbx * kBlock;
+  return v;
+}
+// Part and site of element i (site -1: beyond the range).
+template <bool SCALED>
+__device__ __forceinline__ int vec_site(const VecRange& v, int i, int* part) {
+  if (SCALED) {
+    *part = (i >> 6) & 3;
+    const int s = (i >> 8) * 64 + (i & 63);
+    return s < v.nsx ? v.lo + s : -1;
+  }
+  *part = i / v.nsx;
+  return v.lo + i - *part * v.nsx;
+}
+// Components 3 part .. of site s of a vector.
+template <class SP>
+__device__ __forceinline__ void load_components(const void* v, int stride, int s, int part, cx<typename SP::R>* out) {
+#pragma unroll
+  for (int c = 0; c < 3; ++c) out[c] = SP::load_one(v, stride, s, 3 * part + c);
+}
+// (SP::kScaled: every work-item of the block calls it, with s < 0 where it has nothing to store)
+template <class SP>
+__device__ __forceinline__ void store_components(void* v, int stride, int s, int part, const cx<typename SP::R>* in) {
+  if constexpr (SP::kScaled) {
+    __shared__ float smax[4][64];
+    float m = 0.f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) m = fmaxf(m, fmaxf(fabsf(in[c].re), fabsf(in[c].im)));
+    const int lane = threadIdx.x & 63;
+    __syncthreads();  // the previous step's maxima have been read
+    smax[part][lane] = m;
+    __syncthreads();
+    m = SP::live_scale(fmaxf(fmaxf(smax[0][lane], smax[1][lane]), fmaxf(smax[2][lane], smax[3][lane])));
+    const float inv = m > 0.f ? 1.f / m : 0.f;
+    if (s < 0) return;
+    if (part == 0) SP::store_scale(v, stride, s, m);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) SP::store_one_scaled(v, stride, s, 3 * part + c, in[c], inv);
+  } else {
+    SP::store_part(v, stride, s, part, in);
+  }
+}
+
 template <class SP, bool BATCH>
 __global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table, CgArgs one, int j) {
-  const CgArgs& a = cg_args<BATCH>(table, one);
-  const int k = a.iter0 + a.state->base + j;
-  if (k >= a.state->stop_at) return;
   using R = typename SP::R;
-  const int cur = k & 1;
-  const double* part[2] = {a.pp[cur], a.pq};
+  constexpr int NC = 3;
+  const CgArgs& a = cg_args<BATCH>(table, one);
+  const VecRange w = vec_range<SP::kScaled>(g);
+  cx<R> q[NC] = {}, r[NC] = {};  // (zero where a work-item has no site)
+  auto load = [&](int i) {
+    int part;
+    const int s = vec_site<SP::kScaled>(w, i, &part);
+    if (SP::kScaled && s < 0) return;
+    load_components<SP>(a.q, g.stride, s, part, q);
+    load_components<SP>(a.r, g.stride, s, part, r);
+  };
+  const int k = a.iter0 + a.state->base + j;
+  if (a.mixed) {  // many launches of a mixed chunk are past its stop: they leave before they load
+    if (k >= a.state->stop_at) return;
+    asm volatile("" ::: "memory");
+  }
+  if (w.first < w.nwork) load(w.first);
+  const int stop = a.state->stop_at;
+  asm volatile("" ::: "memory");  // the loads above stay above
+  if (k >= stop) return;
+  const double* part[2] = {a.pp[k & 1], a.pq};
   const int n[2] = {a.n_pp, a.n_pq};
   double sums[2];
   sum_partials_n<kBlock / 64, 2>(part, n, sums);
@@ -243,17 +325,18 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table
   if (blockIdx.x == 0 && threadIdx.x == 0) a.state->alpha = alpha;
   const R al = (R)alpha;
   double v[1] = {0.0};
-  for (int s = blockIdx.x * kBlock + threadIdx.x; s < g.Vh; s += gridDim.x * kBlock) {
-    cx<R> q[12], r[12];
-    SP::load(a.q, g.stride, s, q);
-    SP::load(a.r, g.stride, s, r);
+  for (int i = w.first; i < w.nwork; i += w.step) {
+    if (i != w.first) load(i);
+    int part;
+    const int s = vec_site<SP::kScaled>(w, i, &part);
+    if (!SP::kScaled || s >= 0)
 #pragma unroll
-    for (int m = 0; m < 12; ++m) {
-      r[m].re = fma(-al, q[m].re, r[m].re);
-      r[m].im = fma(-al, q[m].im, r[m].im);
-      v[0] += (double)r[m].re * r[m].re + (double)r[m].im * r[m].im;
-    }
-    SP::store(a.r, g.stride, s, r);
+      for (int m = 0; m < NC; ++m) {
+        r[m].re = fma(-al, q[m].re, r[m].re);
+        r[m].im = fma(-al, q[m].im, r[m].im);
+        v[0] += (double)r[m].re * r[m].re + (double)r[m].im * r[m].im;
+      }
+    store_components<SP>(a.r, g.stride, s, part, r);
   }
   block_sum<1>(v);
   if (threadIdx.x == 0) a.pr[blockIdx.x] = v[0];
@@ -263,53 +346,43 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table
 // precision, when the inner residual fell by delta since the last FP64
 // update), sets stop_at = k + 1; blocks of this launch compare k only, so
 // none of them can observe a change that concerns it.
-//
-// NP work-items share a site: work-item (part, s) updates the colour
-// vectors 12/NP * part .. of site s (NP = 4 only for storages without a
-// per-site scale).  Every input of an element is loaded before any output
-// is stored (x, p and r are distinct arrays), so a work-item makes one
-// round trip to memory.
-template <class SP, class SX, int NP, bool BATCH>
+// Every input of an element is loaded before any output is stored (x, p and r
+// are distinct arrays), so a work-item makes one round trip to memory.
+template <class SP, class SX, bool BATCH>
 __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* table, CgArgs one, int j) {
-  static_assert(NP == 1 || (NP == 4 && !SP::kScaled), "parts need an unscaled storage");
   const CgArgs& a = cg_args<BATCH>(table, one);
   SolverState* stt = a.state;
-  const int k = a.iter0 + stt->base + j;
-  if (k >= stt->stop_at) return;
   using R = typename SP::R;
   using XR = typename SX::R;
-  constexpr int NC = 12 / NP;  // components per work-item
-  const int cur = k & 1, nxt = cur ^ 1;
+  constexpr int NC = 3;  // components per work-item
   const void* src = a.cgls ? a.s : a.r;
-  // XCD x (hardware blocks b with b % 8 == x; gridDim.x is a multiple of
-  // 8) updates the sites [x Vh / 8, (x + 1) Vh / 8), the range the Dslash's
-  // XCD-aware block order gives the same XCD, so p, r and x stay in the L2
-  // of the XCD that reads them next.
-  const int xcd = blockIdx.x & 7, nbx = gridDim.x >> 3;
-  const int lo = (int)((long long)g.Vh * xcd / 8), nsx = (int)((long long)g.Vh * (xcd + 1) / 8) - lo;
-  const int nwork = nsx * NP;
-  cx<R> p[NC], q[NC];
+  const VecRange w = vec_range<SP::kScaled>(g);
+  const int nwork = w.nwork, i0 = w.first;
+  cx<R> p[NC] = {}, q[NC] = {};  // (zero where a work-item has no site)
   cx<XR> x[NC];
   auto load = [&](int i) {
-    const int part = NP == 1 ? 0 : i / nsx;
-    const int s = lo + i - part * nsx;
-    if constexpr (NP == 1) {
-      SP::load(a.p, g.stride, s, p);
-      SX::load(a.x, g.stride, s, x);
-      SP::load(src, g.stride, s, q);
-    } else {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) p[c] = SP::load_one(a.p, g.stride, s, NC * part + c);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) x[c] = SX::load_one(a.x, g.stride, s, NC * part + c);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) q[c] = SP::load_one(src, g.stride, s, NC * part + c);
-    }
+    int part;
+    const int s = vec_site<SP::kScaled>(w, i, &part);
+    if (SP::kScaled && s < 0) return;
+    load_components<SP>(a.p, g.stride, s, part, p);
+    load_components<SX>(a.x, g.stride, s, part, x);
+    load_components<SP>(src, g.stride, s, part, q);
   };
-  // The first element's loads do not depend on the sums: issued before the
-  // reduction, their latency overlaps it.
-  const int i0 = (blockIdx.x >> 3) * kBlock + threadIdx.x;
+  // the state as the launch found it, read once (block 0 writes iters, last,
+  // rr, the other parity's sum_pp, stop_at beyond this label, and maxrr only to
+  // a value that leaves the decision below as it is)
+  const int k = a.iter0 + stt->base + j;
+  if (a.mixed) {  // many launches of a mixed chunk are past its stop: they leave before they load
+    if (k >= stt->stop_at) return;
+    asm volatile("" ::: "memory");
+  }
   if (i0 < nwork) load(i0);
+  const int stop = stt->stop_at, ru_label = stt->ru_label, ru_iter = stt->ru_iter;
+  const int iters = stt->iters;
+  const double thr = stt->thr, maxrr = stt->maxrr, alpha = stt->alpha, sum0 = stt->sum_pp[0], sum1 = stt->sum_pp[1];
+  asm volatile("" ::: "memory");  // the loads above stay above
+  if (k >= stop) return;
+  const int cur = k & 1, nxt = cur ^ 1;
   // the sums of this step in one block reduction (same order, hence the same
   // bits, in every block).  sum(pp[cur]) is the previous iteration's
   // sum(pp[nxt]), which its block 0 left in the state: it is summed again only
@@ -322,7 +395,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
     // eight of them are issued together
     constexpr int U = 8;
     double v[3] = {0.0, 0.0, 0.0};
-    const bool restarted = k == stt->ru_label;
+    const bool restarted = k == ru_label;
     for (int base = threadIdx.x; base < a.n_pp; base += U * kBlock) {
       double t0[U];
 #pragma unroll
@@ -352,39 +425,38 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
       }
     block_sum<3>(v);
     if (threadIdx.x == 0) {
-      bc[0] = v[0], bc[1] = restarted ? v[1] : stt->sum_pp[cur], bc[2] = v[2];
+      bc[0] = v[0], bc[1] = restarted ? v[1] : (cur ? sum1 : sum0), bc[2] = v[2];
       // mixed precision with device-driven updates: does this iteration ask
       // for one?  (Block 0 may already have raised maxrr to max(maxrr, rr):
       // every block gets the same answer.)
       const double r2 = a.cgls ? v[2] : v[0];
       // (ru_iter and ru_label change only between chunks, so every block
       // counts the same iterations.)
-      const int done_after = stt->ru_iter + (k + 1 - stt->ru_label);
-      fold_sh = a.x64 && (r2 <= stt->thr || r2 < a.delta2 * fmax(stt->maxrr, r2) || !(r2 == r2) ||
-                          k + 1 - stt->ru_label >= kMaxInner || (a.max_iters > 0 && done_after >= a.max_iters));
+      const int done_after = ru_iter + (k + 1 - ru_label);
+      fold_sh = a.x64 && (r2 <= thr || r2 < a.delta2 * fmax(maxrr, r2) || !(r2 == r2) ||
+                          k + 1 - ru_label >= kMaxInner || (a.max_iters > 0 && done_after >= a.max_iters));
     }
     __syncthreads();
   }
   const double nw = bc[0], old = bc[1];
   const double rr = a.cgls ? bc[2] : nw;
-  const bool conv = rr <= stt->thr;
-  const double alpha = stt->alpha;
+  const bool conv = rr <= thr;
   // the iteration that asks for an update folds the inner solution into
   // the FP64 one (x64 += xl, xl = 0) for the update that follows
   const bool fold = fold_sh != 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    stt->iters += 1;
+    stt->iters = iters + 1;
     stt->last = k;
     stt->rr = rr;
     stt->sum_pp[nxt] = nw;
     if (a.mixed) {
-      double mx = fmax(stt->maxrr, rr);
+      double mx = fmax(maxrr, rr);
       stt->maxrr = mx;
       // updates also come every kMaxInner iterations, so a low-precision
       // recursion that stagnates cannot run away (the host-driven updates
       // of the solve service: since the restart at ru_label), and, device
       // driven, at the iteration limit
-      if (a.x64 ? fold : (conv || rr < a.delta2 * mx || !(rr == rr) || k + 1 - stt->ru_label >= kMaxInner)) {
+      if (a.x64 ? fold : (conv || rr < a.delta2 * mx || !(rr == rr) || k + 1 - ru_label >= kMaxInner)) {
         stt->reason = 2;
         stt->stop_at = k + 1;
         stt->ru_gate = INT_MAX;  // a device-driven solve updates next
@@ -396,39 +468,37 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
   }
   const bool p_done = conv && !a.mixed;  // converged: the search direction is not needed
   const R beta = (R)(nw / old);
-  for (int i = i0; i < nwork; i += nbx * kBlock) {
-    const int part = NP == 1 ? 0 : i / nsx;
-    const int s = lo + i - part * nsx;
+  for (int i = i0; i < nwork; i += w.step) {
+    int part;
+    const int s = vec_site<SP::kScaled>(w, i, &part);
+    const bool on = !SP::kScaled || s >= 0;
     if (i != i0) load(i);
-    // x += alpha p with the p of this iteration
-#pragma unroll
-    for (int m = 0; m < NC; ++m) {
-      x[m].re = fma((XR)alpha, (XR)p[m].re, x[m].re);
-      x[m].im = fma((XR)alpha, (XR)p[m].im, x[m].im);
-    }
-    if (fold) {
+    if (on) {
+      // x += alpha p with the p of this iteration
 #pragma unroll
       for (int m = 0; m < NC; ++m) {
-        double2* h = (double2*)a.x64 + (size_t)(NP == 1 ? m : NC * part + m) * g.stride + s;
-        const double2 v = *h;
-        *h = make_double2(v.x + (double)x[m].re, v.y + (double)x[m].im);
-        x[m] = {(XR)0, (XR)0};
+        x[m].re = fma((XR)alpha, (XR)p[m].re, x[m].re);
+        x[m].im = fma((XR)alpha, (XR)p[m].im, x[m].im);
       }
-    }
-    if constexpr (NP == 1)
-      SX::store(a.x, g.stride, s, x);
-    else
-      SX::store_part(a.x, g.stride, s, part, x);
-    if (p_done) continue;
+      if (fold) {
 #pragma unroll
-    for (int m = 0; m < NC; ++m) {
-      p[m].re = fma(beta, p[m].re, q[m].re);
-      p[m].im = fma(beta, p[m].im, q[m].im);
+        for (int m = 0; m < NC; ++m) {
+          double2* h = (double2*)a.x64 + (size_t)(NC * part + m) * g.stride + s;
+          const double2 v = *h;
+          *h = make_double2(v.x + (double)x[m].re, v.y + (double)x[m].im);
+          x[m] = {(XR)0, (XR)0};
+        }
+      }
+      store_components<SX>(a.x, g.stride, s, part, x);
     }
-    if constexpr (NP == 1)
-      SP::store(a.p, g.stride, s, p);
-    else
-      SP::store_part(a.p, g.stride, s, part, p);
+    if (p_done) continue;
+    if (on)
+#pragma unroll
+      for (int m = 0; m < NC; ++m) {
+        p[m].re = fma(beta, p[m].re, q[m].re);
+        p[m].im = fma(beta, p[m].im, q[m].im);
+      }
+    store_components<SP>(a.p, g.stride, s, part, p);
   }
 }
 
@@ -685,11 +755,15 @@ static double cg_vec_bytes(hmc_prec prec, bool with_x, int nsp) {
   return (with_x ? 2 * sx : 0.0) + nsp * sp;
 }
 
-hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, int nb, const CgArgs* table,
-                            int nbatch, int j, hipStream_t st) {
+// Blocks of the solver-vector kernels: one share per XCD of a grid that gives
+// every work-item an element up to 2048 blocks (512 to 4096 measure the same).
+int cg_vec_blocks(int Vh) { return std::min(8 * ceil_div(4LL * Vh, 8 * kBlock), 2048); }
+
+hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, const CgArgs* table, int nbatch, int j,
+                            hipStream_t st) {
   // r -= alpha q: q read, r read + written
   TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, false, 3) * g.Vh * nbatch);
-  const dim3 grid(nb, nbatch), block(kBlock);
+  const dim3 grid(cg_vec_blocks(g.Vh), nbatch), block(kBlock);
   auto go = [&](auto kernel_single, auto kernel_batch) {
     if (table)
       hipLaunchKernelGGL(kernel_batch, grid, block, 0, st, to_lat(g), table, a, j);
@@ -705,27 +779,22 @@ hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, int
   return hipGetLastError();
 }
 
-hipError_t launch_cg_pupdate(const LatArg& g, hmc_prec prec, const CgArgs& a, int nb, const CgArgs* table,
-                             int nbatch, int j, hipStream_t st) {
+hipError_t launch_cg_pupdate(const LatArg& g, hmc_prec prec, const CgArgs& a, const CgArgs* table, int nbatch, int j,
+                             hipStream_t st) {
   // x += alpha p, p = r + beta p: x and p read + written, r read
   TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, true, 3) * g.Vh * nbatch);
-  (void)nb;  // the update writes no partial sums: its grid is its own
-  // multiples of 8 blocks (one share per XCD)
-  const int nb4 = std::min(8 * ceil_div(4LL * g.Vh, 8 * kBlock), 2048);
-  const int nb1 = std::min(8 * ceil_div(g.Vh, 8 * kBlock), 2048);
-  const dim3 block(kBlock);
-  auto go = [&](int nb_, auto kernel_single, auto kernel_batch) {
-    const dim3 grid(nb_, nbatch);
+  const dim3 grid(cg_vec_blocks(g.Vh), nbatch), block(kBlock);
+  auto go = [&](auto kernel_single, auto kernel_batch) {
     if (table)
       hipLaunchKernelGGL(kernel_batch, grid, block, 0, st, to_lat(g), table, a, j);
     else
       hipLaunchKernelGGL(kernel_single, grid, block, 0, st, to_lat(g), table, a, j);
   };
   switch (prec) {
-    case HMC_F64: go(nb4, k_cg_pupdate<SpF64, SpF64, 4, false>, k_cg_pupdate<SpF64, SpF64, 4, true>); break;
-    case HMC_F32: go(nb4, k_cg_pupdate<SpF32, SpF32, 4, false>, k_cg_pupdate<SpF32, SpF32, 4, true>); break;
-    case HMC_F16: go(nb1, k_cg_pupdate<SpF16, SpF32, 1, false>, k_cg_pupdate<SpF16, SpF32, 1, true>); break;
-    case HMC_BF16: go(nb4, k_cg_pupdate<SpBF16, SpF32, 4, false>, k_cg_pupdate<SpBF16, SpF32, 4, true>); break;
+    case HMC_F64: go(k_cg_pupdate<SpF64, SpF64, false>, k_cg_pupdate<SpF64, SpF64, true>); break;
+    case HMC_F32: go(k_cg_pupdate<SpF32, SpF32, false>, k_cg_pupdate<SpF32, SpF32, true>); break;
+    case HMC_F16: go(k_cg_pupdate<SpF16, SpF32, false>, k_cg_pupdate<SpF16, SpF32, true>); break;
+    case HMC_BF16: go(k_cg_pupdate<SpBF16, SpF32, false>, k_cg_pupdate<SpBF16, SpF32, true>); break;
   }
   return hipGetLastError();
 }

@@ -35,6 +35,19 @@ template <typename T>
 __device__ __forceinline__ const HMC_GLOBAL T& gld(const void* base, unsigned idx) {
   return *(const HMC_GLOBAL T*)((const HMC_GLOBAL char*)base + idx * (unsigned)sizeof(T));
 }
+// Component array k of a field whose components are `stride` elements of T
+// apart: a scalar base where the arguments are uniform over the wavefront, so
+// that the loads of a site's components share one lane offset instead of
+// computing one each (in the FP32-arithmetic hops 17 vector additions of ~200
+// per hop, and in FP64 17 registers).
+template <typename T>
+__device__ __forceinline__ const void* comp(const void* base, int k, int stride) {
+  return (const char*)base + (size_t)k * (size_t)stride * sizeof(T);
+}
+template <typename T>
+__device__ __forceinline__ void* comp(void* base, int k, int stride) {
+  return (char*)base + (size_t)k * (size_t)stride * sizeof(T);
+}
 // Same, with the non-temporal hint when NT (data used once per sweep, which
 // then leaves the caches to data that is reused).
 template <typename T, bool NT = false>
@@ -531,23 +544,23 @@ struct SpF64 {
   __device__ static void load(const void* base, int stride, int s, cx<R>* v) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-      v2d t = gld<v2d>(base, k * stride + s);
+      v2d t = gld<v2d>(comp<v2d>(base, k, stride), s);
       v[k] = {t.x, t.y};
     }
   }
   template <bool NT = false>
   __device__ static void store(void* base, int stride, int s, const cx<R>* v) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) gput<NT>(base, k * stride + s, v2d{v[k].re, v[k].im});
+    for (int k = 0; k < 12; ++k) gput<NT>(comp<v2d>(base, k, stride), s, v2d{v[k].re, v[k].im});
   }
   // component k of site s
   __device__ static cx<R> load_one(const void* base, int stride, int s, int k) {
-    v2d t = gld<v2d>(base, k * stride + s);
+    v2d t = gld<v2d>(comp<v2d>(base, k, stride), s);
     return {t.x, t.y};
   }
   template <bool NT = false>
   __device__ static void store_one(void* base, int stride, int s, int k, cx<R> v) {
-    gput<NT>(base, k * stride + s, v2d{v.re, v.im});
+    gput<NT>(comp<v2d>(base, k, stride), s, v2d{v.re, v.im});
   }
   // components 3*part .. 3*part+2 of site s
   template <bool NT = false>
@@ -564,22 +577,22 @@ struct SpF32 {
   __device__ static void load(const void* base, int stride, int s, cx<R>* v) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-      v2f t = gld<v2f>(base, k * stride + s);
+      v2f t = gld<v2f>(comp<v2f>(base, k, stride), s);
       v[k] = {t.x, t.y};
     }
   }
   template <bool NT = false>
   __device__ static void store(void* base, int stride, int s, const cx<R>* v) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) gput<NT>(base, k * stride + s, v2f{v[k].re, v[k].im});
+    for (int k = 0; k < 12; ++k) gput<NT>(comp<v2f>(base, k, stride), s, v2f{v[k].re, v[k].im});
   }
   __device__ static cx<R> load_one(const void* base, int stride, int s, int k) {
-    v2f t = gld<v2f>(base, k * stride + s);
+    v2f t = gld<v2f>(comp<v2f>(base, k, stride), s);
     return {t.x, t.y};
   }
   template <bool NT = false>
   __device__ static void store_one(void* base, int stride, int s, int k, cx<R> v) {
-    gput<NT>(base, k * stride + s, v2f{v.re, v.im});
+    gput<NT>(comp<v2f>(base, k, stride), s, v2f{v.re, v.im});
   }
   template <bool NT = false>
   __device__ static void store_part(void* base, int stride, int s, int part, const cx<R>* v) {
@@ -596,7 +609,7 @@ struct SpF16 {
     const float f = gld<float>(base, 12 * stride + s);  // scales follow the 12 components
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-      v2f t = __builtin_convertvector(gld<v2h>(base, k * stride + s), v2f);
+      v2f t = __builtin_convertvector(gld<v2h>(comp<v2h>(base, k, stride), s), v2f);
       v[k] = {t.x * f, t.y * f};
     }
   }
@@ -618,17 +631,17 @@ struct SpF16 {
     gput<NT>(base, 12 * stride + s, m);
 #pragma unroll
     for (int k = 0; k < 12; ++k)
-      gput<NT>(base, k * stride + s, __builtin_convertvector((v2f{v[k].re * inv, v[k].im * inv}), v2h));
+      gput<NT>(comp<v2h>(base, k, stride), s, __builtin_convertvector((v2f{v[k].re * inv, v[k].im * inv}), v2h));
   }
   __device__ static cx<R> load_one(const void* base, int stride, int s, int k) {
     const float f = gld<float>(base, 12 * stride + s);
-    v2f t = __builtin_convertvector(gld<v2h>(base, k * stride + s), v2f);
+    v2f t = __builtin_convertvector(gld<v2h>(comp<v2h>(base, k, stride), s), v2f);
     return {t.x * f, t.y * f};
   }
   // component k of site s, scaled by inv, and the site's scale m itself
   template <bool NT = false>
   __device__ static void store_one_scaled(void* base, int stride, int s, int k, cx<R> v, float inv) {
-    gput<NT>(base, k * stride + s, __builtin_convertvector((v2f{v.re * inv, v.im * inv}), v2h));
+    gput<NT>(comp<v2h>(base, k, stride), s, __builtin_convertvector((v2f{v.re * inv, v.im * inv}), v2h));
   }
   template <bool NT = false>
   __device__ static void store_scale(void* base, int stride, int s, float m) {
@@ -643,22 +656,22 @@ struct SpBF16 {
   __device__ static void load(const void* base, int stride, int s, cx<R>* v) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-      uint32_t w = gld<uint32_t>(base, k * stride + s);
+      uint32_t w = gld<uint32_t>(comp<uint32_t>(base, k, stride), s);
       v[k] = {bf16_to_f(w & 0xffffu), bf16_to_f(w >> 16)};
     }
   }
   template <bool NT = false>
   __device__ static void store(void* base, int stride, int s, const cx<R>* v) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) gput<NT>(base, k * stride + s, f_to_bf16(v[k].re) | (f_to_bf16(v[k].im) << 16));
+    for (int k = 0; k < 12; ++k) gput<NT>(comp<uint32_t>(base, k, stride), s, f_to_bf16(v[k].re) | (f_to_bf16(v[k].im) << 16));
   }
   __device__ static cx<R> load_one(const void* base, int stride, int s, int k) {
-    uint32_t w = gld<uint32_t>(base, k * stride + s);
+    uint32_t w = gld<uint32_t>(comp<uint32_t>(base, k, stride), s);
     return {bf16_to_f(w & 0xffffu), bf16_to_f(w >> 16)};
   }
   template <bool NT = false>
   __device__ static void store_one(void* base, int stride, int s, int k, cx<R> v) {
-    gput<NT>(base, k * stride + s, f_to_bf16(v.re) | (f_to_bf16(v.im) << 16));
+    gput<NT>(comp<uint32_t>(base, k, stride), s, f_to_bf16(v.re) | (f_to_bf16(v.im) << 16));
   }
   template <bool NT = false>
   __device__ static void store_part(void* base, int stride, int s, int part, const cx<R>* v) {
@@ -692,14 +705,31 @@ struct LkF64 {
   }
   // Component K of the link at checkerboard site s of parity par, where mu
   // and par are uniform over the wavefront: the array's base is then a
-  // scalar and the lane's byte offset voff = 16 s is shared by all
-  // components, so a load costs no vector address arithmetic.
-  template <int K>
-  __device__ static cx<R> one_u(const void* base, int stride, int mu, int par, unsigned voff) {
-    const HMC_GLOBAL char* p =
-        (const HMC_GLOBAL char*)base + ((size_t)((mu * 2 + par) * 9 + K) * (size_t)stride) * sizeof(v2d);
-    v2d t = *(const HMC_GLOBAL v2d*)(p + voff);
+  // scalar and the lane's byte offset is shared by all components, so a load
+  // costs no vector address arithmetic.
+  template <int K, bool NT = false>
+  __device__ static cx<R> one_u(const void* base, int stride, int mu, int par, int s) {
+    v2d t = gld_link<v2d, NT>(comp<v2d>(base, (mu * 2 + par) * 9 + K, stride), s);
     return {t.x, t.y};
+  }
+  // load (mu, par uniform) in two steps: the stored reals, and what is rebuilt
+  // from them (nothing here)
+  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
+    u.m[0] = one_u<0>(base, stride, mu, par, s);
+    u.m[1] = one_u<1>(base, stride, mu, par, s);
+    u.m[2] = one_u<2>(base, stride, mu, par, s);
+    u.m[3] = one_u<3>(base, stride, mu, par, s);
+    u.m[4] = one_u<4>(base, stride, mu, par, s);
+    u.m[5] = one_u<5>(base, stride, mu, par, s);
+    u.m[6] = one_u<6>(base, stride, mu, par, s);
+    u.m[7] = one_u<7>(base, stride, mu, par, s);
+    u.m[8] = one_u<8>(base, stride, mu, par, s);
+  }
+  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>&) {}
+  __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
+    mat3<R> u;
+    raw_u(base, stride, mu, par, s, u);
+    return u;
   }
   __device__ static void store(void* base, int stride, int mu, int par, int s, const mat3<R>& u) {
     void* p = (char*)base + (size_t)(mu * 2 + par) * 9 * stride * sizeof(v2d);
@@ -730,6 +760,31 @@ struct LkF32 {
     }
     return u;
   }
+  // the same with mu and par uniform over the wavefront (LkF64::one_u)
+  template <int K, bool NT = false>
+  __device__ static cx<R> one_u(const void* base, int stride, int mu, int par, int s) {
+    v2f t = gld_link<v2f, NT>(comp<v2f>(base, (mu * 2 + par) * 9 + K, stride), s);
+    return {t.x, t.y};
+  }
+  // load (mu, par uniform) in two steps: the stored reals, and what is rebuilt
+  // from them (nothing here)
+  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
+    u.m[0] = one_u<0>(base, stride, mu, par, s);
+    u.m[1] = one_u<1>(base, stride, mu, par, s);
+    u.m[2] = one_u<2>(base, stride, mu, par, s);
+    u.m[3] = one_u<3>(base, stride, mu, par, s);
+    u.m[4] = one_u<4>(base, stride, mu, par, s);
+    u.m[5] = one_u<5>(base, stride, mu, par, s);
+    u.m[6] = one_u<6>(base, stride, mu, par, s);
+    u.m[7] = one_u<7>(base, stride, mu, par, s);
+    u.m[8] = one_u<8>(base, stride, mu, par, s);
+  }
+  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>&) {}
+  __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
+    mat3<R> u;
+    raw_u(base, stride, mu, par, s, u);
+    return u;
+  }
   __device__ static void store(void* base, int stride, int mu, int par, int s, const mat3<double>& u) {
     void* p = (char*)base + (size_t)(mu * 2 + par) * 9 * stride * sizeof(v2f);
 #pragma unroll
@@ -757,6 +812,31 @@ struct LkF16 {
       v2f t = __builtin_convertvector(gld_link<v2h, NT>(p, k * stride + s), v2f);
       u.m[k] = {t.x, t.y};
     }
+    return u;
+  }
+  // the same with mu and par uniform over the wavefront (LkF64::one_u)
+  template <int K, bool NT = false>
+  __device__ static cx<R> one_u(const void* base, int stride, int mu, int par, int s) {
+    v2f t = __builtin_convertvector(gld_link<v2h, NT>(comp<v2h>(base, (mu * 2 + par) * 9 + K, stride), s), v2f);
+    return {t.x, t.y};
+  }
+  // load (mu, par uniform) in two steps: the stored reals, and what is rebuilt
+  // from them (nothing here)
+  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
+    u.m[0] = one_u<0>(base, stride, mu, par, s);
+    u.m[1] = one_u<1>(base, stride, mu, par, s);
+    u.m[2] = one_u<2>(base, stride, mu, par, s);
+    u.m[3] = one_u<3>(base, stride, mu, par, s);
+    u.m[4] = one_u<4>(base, stride, mu, par, s);
+    u.m[5] = one_u<5>(base, stride, mu, par, s);
+    u.m[6] = one_u<6>(base, stride, mu, par, s);
+    u.m[7] = one_u<7>(base, stride, mu, par, s);
+    u.m[8] = one_u<8>(base, stride, mu, par, s);
+  }
+  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>&) {}
+  __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
+    mat3<R> u;
+    raw_u(base, stride, mu, par, s, u);
     return u;
   }
   __device__ static void store(void* base, int stride, int mu, int par, int s, const mat3<double>& u) {
@@ -789,6 +869,31 @@ struct LkBF16 {
     }
     return u;
   }
+  // the same with mu and par uniform over the wavefront (LkF64::one_u)
+  template <int K, bool NT = false>
+  __device__ static cx<R> one_u(const void* base, int stride, int mu, int par, int s) {
+    uint32_t w = gld_link<uint32_t, NT>(comp<uint32_t>(base, (mu * 2 + par) * 9 + K, stride), s);
+    return {bf16_to_f(w & 0xffffu), bf16_to_f(w >> 16)};
+  }
+  // load (mu, par uniform) in two steps: the stored reals, and what is rebuilt
+  // from them (nothing here)
+  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
+    u.m[0] = one_u<0>(base, stride, mu, par, s);
+    u.m[1] = one_u<1>(base, stride, mu, par, s);
+    u.m[2] = one_u<2>(base, stride, mu, par, s);
+    u.m[3] = one_u<3>(base, stride, mu, par, s);
+    u.m[4] = one_u<4>(base, stride, mu, par, s);
+    u.m[5] = one_u<5>(base, stride, mu, par, s);
+    u.m[6] = one_u<6>(base, stride, mu, par, s);
+    u.m[7] = one_u<7>(base, stride, mu, par, s);
+    u.m[8] = one_u<8>(base, stride, mu, par, s);
+  }
+  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>&) {}
+  __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
+    mat3<R> u;
+    raw_u(base, stride, mu, par, s, u);
+    return u;
+  }
   __device__ static void store(void* base, int stride, int mu, int par, int s, const mat3<double>& u) {
     void* p = (char*)base + (size_t)(mu * 2 + par) * 9 * stride * sizeof(uint32_t);
 #pragma unroll
@@ -814,17 +919,20 @@ struct LkRows2 {
   __device__ static mat3<R> load2(const void* base, int stride, int mu, int par, int s) {
     return LK::template load<6, NT>(base, stride, mu, par, s);
   }
-  // the same with mu and par uniform over the wavefront (LK::one_u)
+  // the same with mu and par uniform over the wavefront (LK::one_u), in two
+  // steps: the stored reals, and what is rebuilt from them
+  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
+    u.m[0] = LK::template one_u<0, NT>(base, stride, mu, par, s);
+    u.m[1] = LK::template one_u<1, NT>(base, stride, mu, par, s);
+    u.m[2] = LK::template one_u<2, NT>(base, stride, mu, par, s);
+    u.m[3] = LK::template one_u<3, NT>(base, stride, mu, par, s);
+    u.m[4] = LK::template one_u<4, NT>(base, stride, mu, par, s);
+    u.m[5] = LK::template one_u<5, NT>(base, stride, mu, par, s);
+  }
+  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>& u) { third_row(u); }
   __device__ static mat3<R> load2_u(const void* base, int stride, int mu, int par, int s) {
-    static_assert(!NT, "uniform-parity loads are not streamed");
-    const unsigned v = (unsigned)s * 16u;
     mat3<R> u;
-    u.m[0] = LK::template one_u<0>(base, stride, mu, par, v);
-    u.m[1] = LK::template one_u<1>(base, stride, mu, par, v);
-    u.m[2] = LK::template one_u<2>(base, stride, mu, par, v);
-    u.m[3] = LK::template one_u<3>(base, stride, mu, par, v);
-    u.m[4] = LK::template one_u<4>(base, stride, mu, par, v);
-    u.m[5] = LK::template one_u<5>(base, stride, mu, par, v);
+    raw_u(base, stride, mu, par, s, u);
     return u;
   }
   __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
@@ -869,23 +977,32 @@ struct LkRowCol {
     }
     return u;
   }
-  // the same with mu and par uniform over the wavefront (LK::one_u)
-  __device__ static mat3<R> load2_u(const void* base, int stride, int mu, int par, int s) {
-    static_assert(!NT, "uniform-parity loads are not streamed");
-    const unsigned v = (unsigned)s * 16u;
-    mat3<R> u;
-    u.m[0] = LK::template one_u<0>(base, stride, mu, par, v);
-    u.m[1] = LK::template one_u<1>(base, stride, mu, par, v);
-    u.m[2] = LK::template one_u<2>(base, stride, mu, par, v);
-    u.m[5] = LK::template one_u<5>(base, stride, mu, par, v);
-    u.m[8] = LK::template one_u<8>(base, stride, mu, par, v);
+  // the same with mu and par uniform over the wavefront (LK::one_u), in two
+  // steps: the stored reals, and what is rebuilt from them
+  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
+    u.m[0] = LK::template one_u<0, NT>(base, stride, mu, par, s);
+    u.m[1] = LK::template one_u<1, NT>(base, stride, mu, par, s);
+    u.m[2] = LK::template one_u<2, NT>(base, stride, mu, par, s);
+    u.m[5] = LK::template one_u<5, NT>(base, stride, mu, par, s);
+    u.m[8] = LK::template one_u<8, NT>(base, stride, mu, par, s);
+  }
+  __device__ static void finish2_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
     const R d = norm2(u.m[0]) + norm2(u.m[1]);
     if (d < R(0.0625)) {
-      u.m[3] = LK::template one_u<3>(base, stride, mu, par, v);
-      u.m[4] = LK::template one_u<4>(base, stride, mu, par, v);
+      u.m[3] = LK::template one_u<3, NT>(base, stride, mu, par, s);
+      u.m[4] = LK::template one_u<4, NT>(base, stride, mu, par, s);
     } else {
       solve_row1(u, d);
     }
+  }
+  __device__ static void finish_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
+    finish2_u(base, stride, mu, par, s, u);
+    third_row(u);
+  }
+  __device__ static mat3<R> load2_u(const void* base, int stride, int mu, int par, int s) {
+    mat3<R> u;
+    raw_u(base, stride, mu, par, s, u);
+    finish2_u(base, stride, mu, par, s, u);
     return u;
   }
   __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {

@@ -22,6 +22,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <climits>
+
 #include "device.h"
 #include "internal.h"
 
@@ -69,7 +71,7 @@ __device__ __forceinline__ void hop_dir(const Lat& g, const Site& st, int out_pa
 #pragma unroll
       for (int k = 0; k < 6; ++k) h[k] = sg * h[k];
     }
-    const mat3<R> u = LK::load(U, g.stride, MU, out_par, sl);
+    const mat3<R> u = LK::load_u(U, g.stride, MU, out_par, sl);
     mv(u, h, uh);
     mv(u, h + 3, uh + 3);
     spin_accum<MU, SF>(acc, uh);
@@ -84,7 +86,7 @@ __device__ __forceinline__ void hop_dir(const Lat& g, const Site& st, int out_pa
 #pragma unroll
       for (int k = 0; k < 6; ++k) h[k] = sg * h[k];
     }
-    const mat3<R> u = LK::load(U, g.stride, MU, out_par ^ 1, sn);
+    const mat3<R> u = LK::load_u(U, g.stride, MU, out_par ^ 1, sn);
     mdv(u, h, uh);
     mdv(u, h + 3, uh + 3);
     spin_accum<MU, SB>(acc, uh);
@@ -270,30 +272,34 @@ __global__ void __launch_bounds__(128) k_dslash_split(Lat g, int out_par, const 
   }
 }
 
-// One hop: uh = U h (forward) or U^dag h (backward), h the two projected
-// spin components of the neighbour's spinor, with the time-boundary sign.
-template <class SP, class LK, int MU, int DIR, bool DAG>
-__device__ __forceinline__ void one_hop(const Lat& g, const Site& st, int out_par, int s, const void* U,
-                                        const void* in, cx<typename SP::R>* uh) {
-  using R = typename SP::R;
-  constexpr int SIG = (DIR > 0) == DAG ? +1 : -1;
-  bool wrap;
-  const int sn = neighbour_lex<MU, DIR>(g, st, &wrap) >> 1;
-  cx<R> psi[12], h[6];
-  SP::load(in, g.stride, sn, psi);
-  const mat3<R> u = DIR > 0 ? LK::load(U, g.stride, MU, out_par, s) : LK::load(U, g.stride, MU, out_par ^ 1, sn);
-  spin_project<MU, SIG>(psi, h);
-  if (MU == 3) {
-    const R sg = wrap ? R(-1) : R(1);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) h[k] = sg * h[k];
+// Index of the neighbour of hop w (direction w / 2, forward if w is even);
+// *wrap is set where the hop crosses the boundary.
+__device__ __forceinline__ int hop_neighbour(const Lat& g, const Site& st, int w, bool* wrap) {
+  switch (w) {
+    case 0: return neighbour_lex<0, +1>(g, st, wrap) >> 1;
+    case 1: return neighbour_lex<0, -1>(g, st, wrap) >> 1;
+    case 2: return neighbour_lex<1, +1>(g, st, wrap) >> 1;
+    case 3: return neighbour_lex<1, -1>(g, st, wrap) >> 1;
+    case 4: return neighbour_lex<2, +1>(g, st, wrap) >> 1;
+    case 5: return neighbour_lex<2, -1>(g, st, wrap) >> 1;
+    case 6: return neighbour_lex<3, +1>(g, st, wrap) >> 1;
+    default: return neighbour_lex<3, -1>(g, st, wrap) >> 1;
   }
-  if (DIR > 0) {
-    mv(u, h, uh);
-    mv(u, h + 3, uh + 3);
-  } else {
-    mdv(u, h, uh);
-    mdv(u, h + 3, uh + 3);
+}
+
+// The projected spinor of hop w.
+template <bool DAG, typename R>
+__device__ __forceinline__ void hop_project(int w, const cx<R>* psi, cx<R>* h) {
+  constexpr int SF = DAG ? +1 : -1, SB = -SF;
+  switch (w) {
+    case 0: spin_project<0, SF>(psi, h); break;
+    case 1: spin_project<0, SB>(psi, h); break;
+    case 2: spin_project<1, SF>(psi, h); break;
+    case 3: spin_project<1, SB>(psi, h); break;
+    case 4: spin_project<2, SF>(psi, h); break;
+    case 5: spin_project<2, SB>(psi, h); break;
+    case 6: spin_project<3, SF>(psi, h); break;
+    default: spin_project<3, SB>(psi, h); break;
   }
 }
 
@@ -342,6 +348,7 @@ __device__ __forceinline__ cx<R> hops_combine(const cx<R> (*half)[6][64], int c,
 // 16^3x32 19.6 -> 17.5, FP16 14.9 -> 14.1, BF16 13.7 -> 12.7; FP64 24^3x48
 // with streaming 161 -> 158.
 constexpr int kHopThreads = 8 * 64;
+constexpr int kAlphaAhead = 2;  // partial sums per work-item requested ahead (1024 in all, a 2^16-site launch's)
 
 template <class SP, class LK, bool DAG, int EPI, bool BATCH>
 __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par, const DslashArgs* __restrict__ table,
@@ -355,9 +362,33 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
   else
     ep = &one;
   const DslashArgs& e = *ep;
-  const int label = e.iter0 + j + (e.label_base ? *(const HMC_GLOBAL int*)e.label_base : 0);
-  if (e.stop_at && label >= *(const HMC_GLOBAL int*)e.stop_at) return;
-  alpha_prologue<8>(e, label);
+  // Everything the hop reads is requested before anything is waited for: the
+  // solver control, the step length, block 0's partial sums, the epilogue's
+  // inputs, the spinor and the link.  A launch past the stop then reads them in
+  // vain, so launches of which many are past it look at the control first: the
+  // low-precision iterations queued up to the next reliable update, and the
+  // gated launches of the update itself (which have no label base).
+  const int base = e.label_base ? *(const HMC_GLOBAL int*)e.label_base : 0;
+  const int label = e.iter0 + j + base;
+  int stop = INT_MAX;
+  if (sizeof(R) == 4 || !e.label_base) {
+    if (e.stop_at && label >= *(const HMC_GLOBAL int*)e.stop_at) return;
+    asm volatile("" ::: "memory");  // (or the compiler waits for the control on both paths)
+  } else if (e.stop_at) {
+    stop = *(const HMC_GLOBAL int*)e.stop_at;
+  }
+  const double alpha = EPI == EPI_CG ? *(const HMC_GLOBAL double*)e.alpha_in : 0.0;
+  const bool sums = EPI == EPI_PLAIN && e.alpha_out && blockIdx.x == 0;
+  double ta[kAlphaAhead], tb[kAlphaAhead];
+  if (sums) {
+    const double* pp = e.alpha_pp[label & 1];
+#pragma unroll
+    for (int u = 0; u < kAlphaAhead; ++u) {
+      const int i = threadIdx.x + u * kHopThreads;
+      ta[u] = i < e.alpha_n_pp ? pp[i] : 0.0;
+      tb[u] = i < e.alpha_n_den ? e.alpha_den[i] : 0.0;
+    }
+  }
   const int b = xcd_remap(blockIdx.x, gridDim.x);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ls = threadIdx.x & (kSites - 1);
@@ -365,9 +396,12 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
   const bool active = s < g.Vh;
   // wavefront w combines spin w % 4, colours 0 and 1 (w < 4) or 2 (w >= 4)
   const int spin = w & 3, c0 = w < 4 ? 0 : 2, nc = w < 4 ? 2 : 1;
-  cx<R> yv[2], rv[2];
+  const int lmu = w >> 1, lpar = out_par ^ (w & 1);
+  int lsite = s;
+  bool wrap = false;
+  cx<R> yv[2], rv[2], psi[12];
+  mat3<R> u;
   if (active) {
-    // the epilogue's inputs are requested with the hop's, not after it
     if (EPI != EPI_PLAIN && e.y)
 #pragma unroll
       for (int q = 0; q < 2; ++q)
@@ -377,16 +411,27 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
       for (int q = 0; q < 2; ++q)
         if (q < nc) rv[q] = SP::load_one(e.r, g.stride, s, 3 * spin + c0 + q);
     const Site st = cb_site(g, out_par, s);
-    cx<R> uh[6];
-    switch (w) {
-      case 0: one_hop<SP, LK, 0, +1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
-      case 1: one_hop<SP, LK, 0, -1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
-      case 2: one_hop<SP, LK, 1, +1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
-      case 3: one_hop<SP, LK, 1, -1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
-      case 4: one_hop<SP, LK, 2, +1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
-      case 5: one_hop<SP, LK, 2, -1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
-      case 6: one_hop<SP, LK, 3, +1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
-      default: one_hop<SP, LK, 3, -1, DAG>(g, st, out_par, s, e.U, e.in, uh); break;
+    const int sn = hop_neighbour(g, st, w, &wrap);
+    if (w & 1) lsite = sn;  // a backward hop's link belongs to the neighbour
+    SP::load(e.in, g.stride, sn, psi);
+    LK::raw_u(e.U, g.stride, lmu, lpar, lsite, u);
+  }
+  asm volatile("" ::: "memory");  // the loads above stay above
+  if (label >= stop) return;
+  if (active) {
+    // the spinor's registers are free before the link is rebuilt
+    cx<R> h[6], uh[6];
+    hop_project<DAG>(w, psi, h);
+    if (w >= 6 && wrap)  // the time boundary's sign
+#pragma unroll
+      for (int k = 0; k < 6; ++k) h[k] = -h[k];
+    LK::finish_u(e.U, g.stride, lmu, lpar, lsite, u);
+    if (w & 1) {
+      mdv(u, h, uh);
+      mdv(u, h + 3, uh + 3);
+    } else {
+      mv(u, h, uh);
+      mv(u, h + 3, uh + 3);
     }
 #pragma unroll
     for (int k = 0; k < 6; ++k) half[w][k][ls] = uh[k];
@@ -413,7 +458,7 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
           o[q] = bb * o[q];
       }
       if (EPI == EPI_CG) {
-        const R al = (R)(*(const HMC_GLOBAL double*)e.alpha_in);
+        const R al = (R)alpha;
         o[q] = {fma(-al, o[q].re, rv[q].re), fma(-al, o[q].im, rv[q].im)};
       }
       if (EPI == EPI_AXPY_NORM || EPI == EPI_CG)
@@ -446,6 +491,16 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
   if (EPI == EPI_AXPY_NORM || EPI == EPI_CG) {
     block_sum<1, 8>(nrm);
     put_partial(e, label, b, nrm[0]);
+  }
+  if (sums) {  // the step length for the next hop, after this one's stores
+    double v[2] = {0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < kAlphaAhead; ++q) v[0] += ta[q], v[1] += tb[q];
+    const double* pp = e.alpha_pp[label & 1];
+    for (int i = threadIdx.x + kAlphaAhead * kHopThreads; i < e.alpha_n_pp; i += kHopThreads) v[0] += pp[i];
+    for (int i = threadIdx.x + kAlphaAhead * kHopThreads; i < e.alpha_n_den; i += kHopThreads) v[1] += e.alpha_den[i];
+    block_sum<2, 8>(v);
+    if (threadIdx.x == 0) *(HMC_GLOBAL double*)e.alpha_out = v[0] / v[1];
   }
 }
 

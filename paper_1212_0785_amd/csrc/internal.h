@@ -218,7 +218,7 @@ struct CgArgs {
   const void* s;   // CGLS: Mhat^dag r
   double* pp[2];   // ping-pong partials: CG |r|^2 (n_pp = blas blocks), CGLS |s|^2 (site blocks)
   double* pq;      // CG <p, A p> = |Mhat p|^2, CGLS |q|^2 (site blocks, from the Dslash epilogue)
-  double* pr;      // CGLS |r|^2 written by the update (blas blocks)
+  double* pr;      // CGLS |r|^2 written by the update (cg_vec_blocks)
   int n_pp, n_pq, n_pr;
   SolverState* state;
   int iter0;       // label offset (the state's base is added)
@@ -231,10 +231,12 @@ struct CgArgs {
 };
 hipError_t launch_cg_init(const LatArg& g, hmc_prec prec, const void* b, void* x, void* r, void* p, double* part,
                           int nb, hipStream_t st);
-hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, int nb, const CgArgs* table,
-                            int nbatch, int j, hipStream_t st);
-hipError_t launch_cg_pupdate(const LatArg& g, hmc_prec prec, const CgArgs& a, int nb, const CgArgs* table,
-                             int nbatch, int j, hipStream_t st);
+// Blocks of the two launches below, and the |r|^2 partials of the first.
+int cg_vec_blocks(int Vh);
+hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, const CgArgs* table, int nbatch, int j,
+                            hipStream_t st);
+hipError_t launch_cg_pupdate(const LatArg& g, hmc_prec prec, const CgArgs& a, const CgArgs* table, int nbatch, int j,
+                             hipStream_t st);
 // Start (reset_iters: counts, base and the device-driven fields cleared) or
 // resume a solve: stop_at = INT_MAX, reason = 0, maxrr from a device slot
 // (null -> 0), stop threshold thr; label >= 0 sets ru_label, the label of the

@@ -91,7 +91,10 @@ size_t carve_request(char* base, const LatArg& g, int prec, SolveVecs* v, void**
   s.pp[0] = (double*)c.take(np * 8);
   s.pp[1] = (double*)c.take(np * 8);
   s.pq = (double*)c.take(np * 8);
-  s.pr = (double*)c.take((size_t)nbR * 8);
+  (void)c.take((size_t)nbR * 8);
+  // the update's partials (at most one per 64 sites) use the odd half of the
+  // solution, which is written when the solve ends
+  s.pr = *x ? (double*)((char*)*x + h64) : nullptr;
   s.red = (double*)c.take((size_t)2 * nbR * 8);
   s.nbD = nbD;
   s.nbR = nbR;
@@ -446,7 +449,7 @@ struct Service {
       build_iteration(r0->v, 0, 0, 0, &one);
       for (int j = 0; j < chunk; ++j)
         HMC_CHECK_HIP(launch_iteration(gr->g, (hmc_prec)prm.inner_prec, 1, &t, one, (int)gr->members.size(),
-                                       r0->v.nbD, r0->v.nbR, gr->J + j, gr->stream));
+                                       gr->J + j, gr->stream));
       gr->J += chunk;
     }
     HMC_CHECK_HIP(sync_all());

@@ -94,7 +94,7 @@ void build_iteration(const SolveVecs& v, int iter0, int mixed, double delta2, It
   c.pr = v.pr;
   c.n_pp = v.nbD;  // |r|^2 (CG) or |s|^2 (CGLS), both from a Dslash epilogue
   c.n_pq = v.nbD;
-  c.n_pr = v.nbR;
+  c.n_pr = cg_vec_blocks(v.g.Vh);
   c.state = v.state;
   c.iter0 = iter0;
   c.cgls = v.cgls;
@@ -106,14 +106,13 @@ void build_iteration(const SolveVecs& v, int iter0, int mixed, double delta2, It
 }
 
 hipError_t launch_iteration(const LatArg& g, hmc_prec prec, int cgls, const IterTables* tab, const IterArgs& one,
-                            int nbatch, int nbD, int nbR, int j, hipStream_t st) {
-  (void)nbD;
+                            int nbatch, int j, hipStream_t st) {
   hipError_t e;
   auto D = [&](int i, int out_par, int dag, int epi) {
     return launch_dslash(prec, dag, epi, g, out_par, tab ? tab->d[i] : nullptr, nbatch, one.d[i], st, j);
   };
-  auto UPD = [&](int i) { return launch_cg_update(g, prec, one.c[i], nbR, tab ? tab->c[i] : nullptr, nbatch, j, st); };
-  auto PUP = [&](int i) { return launch_cg_pupdate(g, prec, one.c[i], nbR, tab ? tab->c[i] : nullptr, nbatch, j, st); };
+  auto UPD = [&](int i) { return launch_cg_update(g, prec, one.c[i], tab ? tab->c[i] : nullptr, nbatch, j, st); };
+  auto PUP = [&](int i) { return launch_cg_pupdate(g, prec, one.c[i], tab ? tab->c[i] : nullptr, nbatch, j, st); };
   if (!cgls) {
     // the four hops are consecutive: one timing sample brackets them all
     timing_group_begin(TK_DSLASH, 4);
@@ -267,7 +266,7 @@ struct ChunkExtra {
 // (mixed precision) the gated reliable update.
 hipError_t chunk_launches(const SolveVecs& v, const IterArgs& args, int n, const ChunkExtra& x, hipStream_t st) {
   for (int j = 0; j < n; ++j) {
-    hipError_t e = launch_iteration(v.g, v.prec, v.cgls, nullptr, args, 1, v.nbD, v.nbR, j, st);
+    hipError_t e = launch_iteration(v.g, v.prec, v.cgls, nullptr, args, 1, j, st);
     if (e != hipSuccess) return e;
   }
   // the update's last kernel advances the label base itself
@@ -404,7 +403,7 @@ hipError_t enqueue_chunk(Fields* F, const SolveVecs& v, const IterArgs& args, co
                          const ChunkExtra& x = ChunkExtra{}) {
   if (!x.ru && !chunk_records(x)) {
     for (int j = 0; j < c.n; ++j) {
-      hipError_t e = launch_iteration(v.g, v.prec, v.cgls, nullptr, args, 1, v.nbD, v.nbR, c.k + j, st);
+      hipError_t e = launch_iteration(v.g, v.prec, v.cgls, nullptr, args, 1, c.k + j, st);
       if (e != hipSuccess) return e;
     }
   } else {

@@ -57,7 +57,7 @@ struct IterTables {
 
 // Launch one iteration (label iter0 + j per entry).
 hipError_t launch_iteration(const LatArg& g, hmc_prec prec, int cgls, const IterTables* tab, const IterArgs& one,
-                            int nbatch, int nbD, int nbR, int j, hipStream_t st);
+                            int nbatch, int j, hipStream_t st);
 
 // FP64 helpers on one solve (single-entry launches).
 hipError_t mhat64(const SolveVecs& v, void* out, const void* in, int dag, double* partial, hipStream_t st);

@@ -261,18 +261,19 @@ int dslash_shape(const LatArg& g, hmc_prec prec) {
   if (forced > 0) return forced;
   const int t = tune_lookup(g.L, TUNE_DSLASH, prec);
   if (t > 0) return t;
-  // One wavefront per hop while the latency of a hop's loads counts, one site
-  // per work-item once the launch fills the chip many times over; FP64 between
-  // them in two wavefronts per site (measured, Mhat in us, 1 / 2 / 4:
-  // 16^3x32 FP64 34.6 / 31.1 / 29.7, FP32 21.3 / 19.3 / 17.4, BF16 15.9 / 14.7
-  // / 12.4; 24^3x48 FP64 182 / 159 / 157, FP32 88 / 74 / 68, BF16 43.9 / 42.1
-  // / 40.7; 32^3x64 FP64 507 / 479 / 478, FP32 261 / 260 / 254, BF16 138 / 148
-  // / 151; in a solve, where the split shapes' norms have four times the
-  // partial sums, us per iteration: 24^3x48 FP32 291 / 271 / 270, FP16 203 /
-  // 206 / 215, BF16 186 / 193 / 196; 32^3x64 FP64 1243 / 1222 / 1257, FP32 844
-  // / 894 / 887; 40^3x80 FP64 Mhat, tiled / 2: 1274 / 1328)
+  // One wavefront per hop until the launch fills the chip so many times over
+  // that the one-site kernel's smaller traffic wins: FP64 up to 36x28x32x72
+  // sites, whence the tiled order keeps neighbours in L2; the narrower
+  // storages sooner, whose hop is bound by its instructions (measured, Mhat in
+  // us, 1 / 2 / 4: FP64 16^3x32 35 / 32 / 29, 24^3x48 184 / 164 / 154, 32^3x64
+  // 529 / 486 / 462, 36x28x32x72 539 / 563 / 526, 40^3x80 1247 / 1322 / 1280;
+  // FP32 16^3x32 21.3 / 19.3 / 17.4, 24^3x48 88 / 74 / 68, 32^3x64 261 / 260 /
+  // 254; BF16 16^3x32 15.9 / 14.7 / 12.4, 32^3x64 138 / 148 / 151; in a solve,
+  // whose p-update adds four times the partial sums of the split shapes, us
+  // per iteration: FP32 24^3x48 291 / 271 / 270, 32^3x64 844 / 894 / 887; FP16
+  // 24^3x48 203 / 206 / 215; BF16 186 / 193 / 196)
   // (below one block the choice has no effect: dslash_run_shape)
-  if (prec == HMC_F64) return g.Vh < kThreads ? 1 : g.Vh < (1 << 19) ? 4 : g.Vh < 3 << 19 ? 2 : 1;
+  if (prec == HMC_F64) return g.Vh < kThreads ? 1 : g.Vh < 3 << 19 ? 4 : 1;
   return g.Vh < (prec == HMC_F32 ? 1 << 19 : 1 << 18) ? 4 : 1;
 }
 
