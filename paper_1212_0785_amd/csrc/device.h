@@ -256,6 +256,22 @@ __device__ __forceinline__ void third_row(mat3<R>& u) {
   u.m[8] = conj(u.m[0] * u.m[4] - u.m[1] * u.m[3]);
 }
 
+// The same where the third entry of row 2 is stored.
+template <typename R>
+__device__ __forceinline__ void third_row_but_last(mat3<R>& u) {
+  u.m[6] = conj(u.m[1] * u.m[5] - u.m[2] * u.m[4]);
+  u.m[7] = conj(u.m[2] * u.m[3] - u.m[0] * u.m[5]);
+}
+
+// 1 / d for d in [1/16, 2]: in FP32 the hardware's reciprocal and one Newton
+// step, which leaves it within half an ulp and a bit of 1 / d (three
+// operations instead of the ten of a division for any operands).
+__device__ __forceinline__ float inverse_of(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return fmaf(fmaf(-d, r, 1.f), r, r);
+}
+__device__ __forceinline__ double inverse_of(double d) { return 1.0 / d; }
+
 template <typename R>
 __device__ __forceinline__ void reunitarise(mat3<R>& u) {
   R n0 = norm2(u.m[0]) + norm2(u.m[1]) + norm2(u.m[2]);
@@ -528,10 +544,10 @@ __device__ __forceinline__ int dslash_site(const Lat& g, int* part) {
 // need no scale: every |U_ij| <= 1).
 
 __device__ __forceinline__ float bf16_to_f(uint32_t h) { return __uint_as_float(h << 16); }
-__device__ __forceinline__ uint32_t f_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
-  return u >> 16;
+// Two floats rounded to nearest even bfloat16, in one word (one instruction).
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{lo, hi}), v2bf));
 }
 
 // Loads and stores take a base pointer (uniform across the wave) and a
@@ -613,6 +629,32 @@ struct SpF16 {
       v[k] = {t.x * f, t.y * f};
     }
   }
+  // Half spinor (1 + SIG gamma_MU) psi of site s: each of its twelve reals is a
+  // sum of two stored halves times the scale, taken in two mixed-precision
+  // multiply-adds (converting and scaling every component first took five
+  // operations per real; the FP16 hop is bound by its instructions).
+  template <int MU, int SIG>
+  __device__ static void load_projected(const void* base, int stride, int s, cx<R>* h) {
+    const float f = gld<float>(base, 12 * stride + s);
+    v2h t[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) t[k] = gld<v2h>(comp<v2h>(base, k, stride), s);
+    // p +- q, p +- i q scaled
+    auto add = [f](v2h p, v2h q, float sg) {
+      return cx<R>{fmaf((float)p.x, f, sg * fmaf((float)q.x, f, 0.f)), fmaf((float)p.y, f, sg * fmaf((float)q.y, f, 0.f))};
+    };
+    auto add_i = [f](v2h p, v2h q, float sg) {
+      return cx<R>{fmaf((float)p.x, f, -sg * fmaf((float)q.y, f, 0.f)), fmaf((float)p.y, f, sg * fmaf((float)q.x, f, 0.f))};
+    };
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const v2h p0 = t[c], p1 = t[3 + c], p2 = t[6 + c], p3 = t[9 + c];
+      if (MU == 0) h[c] = add_i(p0, p3, SIG), h[3 + c] = add_i(p1, p2, SIG);
+      if (MU == 1) h[c] = add(p0, p3, -SIG), h[3 + c] = add(p1, p2, SIG);
+      if (MU == 2) h[c] = add_i(p0, p2, SIG), h[3 + c] = add_i(p1, p3, -SIG);
+      if (MU == 3) h[c] = add(p0, p2, SIG), h[3 + c] = add(p1, p3, SIG);
+    }
+  }
   // A site whose largest component is below the smallest normal float is
   // stored as zero: 1/m would overflow to infinity.  Such sites arise where
   // a field spreads from a point: each hop onto a new site carries the
@@ -663,7 +705,7 @@ struct SpBF16 {
   template <bool NT = false>
   __device__ static void store(void* base, int stride, int s, const cx<R>* v) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) gput<NT>(comp<uint32_t>(base, k, stride), s, f_to_bf16(v[k].re) | (f_to_bf16(v[k].im) << 16));
+    for (int k = 0; k < 12; ++k) gput<NT>(comp<uint32_t>(base, k, stride), s, pack_bf16(v[k].re, v[k].im));
   }
   __device__ static cx<R> load_one(const void* base, int stride, int s, int k) {
     uint32_t w = gld<uint32_t>(comp<uint32_t>(base, k, stride), s);
@@ -671,7 +713,7 @@ struct SpBF16 {
   }
   template <bool NT = false>
   __device__ static void store_one(void* base, int stride, int s, int k, cx<R> v) {
-    gput<NT>(comp<uint32_t>(base, k, stride), s, f_to_bf16(v.re) | (f_to_bf16(v.im) << 16));
+    gput<NT>(comp<uint32_t>(base, k, stride), s, pack_bf16(v.re, v.im));
   }
   template <bool NT = false>
   __device__ static void store_part(void* base, int stride, int s, int part, const cx<R>* v) {
@@ -898,7 +940,7 @@ struct LkBF16 {
     void* p = (char*)base + (size_t)(mu * 2 + par) * 9 * stride * sizeof(uint32_t);
 #pragma unroll
     for (int k = 0; k < 9; ++k)
-      gst<uint32_t>(p, k * stride + s) = f_to_bf16((float)u.m[k].re) | (f_to_bf16((float)u.m[k].im) << 16);
+      gst<uint32_t>(p, k * stride + s) = pack_bf16((float)u.m[k].re, (float)u.m[k].im);
   }
 };
 
@@ -957,7 +999,7 @@ struct LkRowCol {
   static constexpr bool kStream = NT;  // non-temporal link loads (and output stores)
   __device__ static mat3<R> load(const void* base, int stride, int mu, int par, int s) {
     mat3<R> u = load2(base, stride, mu, par, s);
-    third_row(u);
+    third_row_but_last(u);
     return u;
   }
   // rows 0 and 1 only (row 2 not set)
@@ -997,7 +1039,7 @@ struct LkRowCol {
   }
   __device__ static void finish_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
     finish2_u(base, stride, mu, par, s, u);
-    third_row(u);
+    third_row_but_last(u);
   }
   __device__ static mat3<R> load2_u(const void* base, int stride, int mu, int par, int s) {
     mat3<R> u;
@@ -1007,13 +1049,13 @@ struct LkRowCol {
   }
   __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
     mat3<R> u = load2_u(base, stride, mu, par, s);
-    third_row(u);
+    third_row_but_last(u);
     return u;
   }
   // u10 = -(u00 conj(u02) u12 + conj(u01) conj(u22)) / D
   // u11 = (conj(u00) conj(u22) - u01 conj(u02) u12) / D
   __device__ static void solve_row1(mat3<R>& u, R d) {
-    const R inv = R(1) / d;
+    const R inv = inverse_of(d);
     const cx<R> w = conj(u.m[2]) * u.m[5];
     u.m[3] = (-inv) * (u.m[0] * w + conj(u.m[1]) * conj(u.m[8]));
     u.m[4] = inv * (conj(u.m[0]) * conj(u.m[8]) - u.m[1] * w);

@@ -52,6 +52,18 @@ __device__ __forceinline__ int chain(int idx, cx<R>* acc) {
   return idx;
 }
 
+// Half spinor (1 + SIG gamma_MU) psi of site s.
+template <class SP, int MU, int SIG>
+__device__ __forceinline__ void load_projected(const void* in, int stride, int s, cx<typename SP::R>* h) {
+  if constexpr (SP::kScaled) {
+    SP::template load_projected<MU, SIG>(in, stride, s, h);
+  } else {
+    cx<typename SP::R> psi[12];
+    SP::load(in, stride, s, psi);
+    spin_project<MU, SIG>(psi, h);
+  }
+}
+
 template <class SP, class LK, int MU, bool DAG>
 __device__ __forceinline__ void hop_dir(const Lat& g, const Site& st, int out_par, int s, const void* U,
                                         const void* in, cx<typename SP::R>* acc) {
@@ -62,10 +74,9 @@ __device__ __forceinline__ void hop_dir(const Lat& g, const Site& st, int out_pa
   const int lf = neighbour_lex<MU, +1>(g, st, &wf);
   const int lb = neighbour_lex<MU, -1>(g, st, &wb);
   {
-    cx<R> psi[12], h[6], uh[6];
+    cx<R> h[6], uh[6];
     const int sn = chain(lf >> 1, acc), sl = chain(s, acc);
-    SP::load(in, g.stride, sn, psi);
-    spin_project<MU, SF>(psi, h);
+    load_projected<SP, MU, SF>(in, g.stride, sn, h);
     if (MU == 3) {  // antiperiodic time boundary
       const R sg = wf ? R(-1) : R(1);
 #pragma unroll
@@ -77,10 +88,9 @@ __device__ __forceinline__ void hop_dir(const Lat& g, const Site& st, int out_pa
     spin_accum<MU, SF>(acc, uh);
   }
   {
-    cx<R> psi[12], h[6], uh[6];
+    cx<R> h[6], uh[6];
     const int sn = HMC_HOP_CHAIN == 1 ? chain(lb >> 1, acc) : lb >> 1;
-    SP::load(in, g.stride, sn, psi);
-    spin_project<MU, SB>(psi, h);
+    load_projected<SP, MU, SB>(in, g.stride, sn, h);
     if (MU == 3) {
       const R sg = wb ? R(-1) : R(1);
 #pragma unroll
