@@ -1091,6 +1091,19 @@ __device__ __forceinline__ void store_compact(double* P, int stride, int mu, int
 
 // ------------------------------------------------------------ Philox
 
+// Both halves of a 64 x 64 bit product from four 32 x 32 multiply-adds (taken
+// separately, low and high half need seven; these quarter-rate multiplications
+// are most of what a random number costs).  No sum overflows: a 32 x 32 product
+// plus two 32-bit numbers is below 2^64.
+__device__ __forceinline__ void mul_wide(uint64_t a, uint64_t b, uint64_t* hi, uint64_t* lo) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+  const uint64_t t0 = (uint64_t)a0 * b0;
+  const uint64_t t1 = (uint64_t)a1 * b0 + (t0 >> 32);
+  const uint64_t t2 = (uint64_t)a0 * b1 + (uint32_t)t1;
+  *hi = (uint64_t)a1 * b1 + (t1 >> 32) + (t2 >> 32);
+  *lo = (t2 << 32) | (uint32_t)t0;
+}
+
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11): 10 rounds of two
 // 64x64->128 multiplications with the Weyl key schedule.
 __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
@@ -1099,8 +1112,9 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t
   const uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    uint64_t hi0 = __umul64hi(M0, c0), lo0 = M0 * c0;
-    uint64_t hi1 = __umul64hi(M1, c2), lo1 = M1 * c2;
+    uint64_t hi0, lo0, hi1, lo1;
+    mul_wide(M0, c0, &hi0, &lo0);
+    mul_wide(M1, c2, &hi1, &lo1);
     uint64_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0;
     c1 = lo1;
@@ -1118,12 +1132,13 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t
 // Uniform on (0,1): top 53 bits plus one half, scaled by 2^-53 (exact).
 __device__ __forceinline__ double u53(uint64_t w) { return ((double)(w >> 11) + 0.5) * 0x1p-53; }
 
-// Box-Muller pair from two words.
+// Box-Muller pair from two words.  The angle is a fraction of a turn: 2 u is
+// exact and sincospi reduces it exactly, where sincos(2 pi u) first rounds the
+// product and then reduces it again.
 __device__ __forceinline__ void box_muller(uint64_t w0, uint64_t w1, double* g0, double* g1) {
   double r = sqrt(-2.0 * log(u53(w0)));
-  double th = 6.283185307179586476925286766559 * u53(w1);
   double sn, cs;
-  sincos(th, &sn, &cs);
+  sincospi(2.0 * u53(w1), &sn, &cs);
   *g0 = r * cs;
   *g1 = r * sn;
 }
