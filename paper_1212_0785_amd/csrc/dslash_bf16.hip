@@ -9,4 +9,9 @@ hipError_t launch_dslash_bf16(int dagger, int epi, const LatArg& g, int out_par,
   return launch_links<SpBF16, LkBF16>(HMC_BF16, dagger, epi, g, out_par, table, nbatch, one, st, j);
 }
 
+hipError_t launch_mhat_small_bf16(int dagger, const LatArg& g, const void* U, const void* in, void* out, double b,
+                              bool su3, hipStream_t st) {
+  return launch_mhat_small_links<SpBF16, LkBF16>(HMC_BF16, dagger, g, U, in, out, b, su3, st);
+}
+
 }  // namespace hmc

@@ -9,4 +9,9 @@ hipError_t launch_dslash_f64(int dagger, int epi, const LatArg& g, int out_par, 
   return launch_links<SpF64, LkF64>(HMC_F64, dagger, epi, g, out_par, table, nbatch, one, st, j);
 }
 
+hipError_t launch_mhat_small_f64(int dagger, const LatArg& g, const void* U, const void* in, void* out, double b,
+                              bool su3, hipStream_t st) {
+  return launch_mhat_small_links<SpF64, LkF64>(HMC_F64, dagger, g, U, in, out, b, su3, st);
+}
+
 }  // namespace hmc

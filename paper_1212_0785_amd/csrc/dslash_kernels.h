@@ -313,6 +313,27 @@ __device__ __forceinline__ void hop_project(int w, const cx<R>* psi, cx<R>* h) {
   }
 }
 
+// Hop w's half spinor uh = U h (forward) or U^dag h (backward), h the projected
+// neighbour with the time boundary's sign.  The spinor's registers are free
+// before the rest of the link is rebuilt.
+template <class LK, bool DAG, typename R>
+__device__ __forceinline__ void hop_half(const Lat& g, const void* U, int w, int lpar, int lsite, bool wrap,
+                                         const cx<R>* psi, mat3<R>& u, cx<R>* uh) {
+  cx<R> h[6];
+  hop_project<DAG>(w, psi, h);
+  if (w >= 6 && wrap)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) h[k] = -h[k];
+  LK::finish_u(U, g.stride, w >> 1, lpar, lsite, u);
+  if (w & 1) {
+    mdv(u, h, uh);
+    mdv(u, h + 3, uh + 3);
+  } else {
+    mv(u, h, uh);
+    mv(u, h + 3, uh + 3);
+  }
+}
+
 // Adds hop (MU, SIG)'s share of spin component SPIN, colour c, to acc.
 template <int MU, int SIG, int SPIN, typename R>
 __device__ __forceinline__ cx<R> hop_share(cx<R> acc, const cx<R> (*h)[64], int c, int ls) {
@@ -340,6 +361,16 @@ __device__ __forceinline__ cx<R> hops_combine(const cx<R> (*half)[6][64], int c,
   t = hop_share<3, SF, SPIN>(t, half[6], c, ls);
   t = hop_share<3, SB, SPIN>(t, half[7], c, ls);
   return t;
+}
+
+template <bool DAG, typename R>
+__device__ __forceinline__ cx<R> hops_component(const cx<R> (*half)[6][64], int spin, int c, int ls) {
+  switch (spin) {
+    case 0: return hops_combine<DAG, 0>(half, c, ls);
+    case 1: return hops_combine<DAG, 1>(half, c, ls);
+    case 2: return hops_combine<DAG, 2>(half, c, ls);
+    default: return hops_combine<DAG, 3>(half, c, ls);
+  }
 }
 
 // Four-way direction split, one wavefront per hop: a block of eight
@@ -429,20 +460,8 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
   asm volatile("" ::: "memory");  // the loads above stay above
   if (label >= stop) return;
   if (active) {
-    // the spinor's registers are free before the link is rebuilt
-    cx<R> h[6], uh[6];
-    hop_project<DAG>(w, psi, h);
-    if (w >= 6 && wrap)  // the time boundary's sign
-#pragma unroll
-      for (int k = 0; k < 6; ++k) h[k] = -h[k];
-    LK::finish_u(e.U, g.stride, lmu, lpar, lsite, u);
-    if (w & 1) {
-      mdv(u, h, uh);
-      mdv(u, h + 3, uh + 3);
-    } else {
-      mv(u, h, uh);
-      mv(u, h + 3, uh + 3);
-    }
+    cx<R> uh[6];
+    hop_half<LK, DAG>(g, e.U, w, lpar, lsite, wrap, psi, u, uh);
 #pragma unroll
     for (int k = 0; k < 6; ++k) half[w][k][ls] = uh[k];
   }
@@ -454,12 +473,7 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
     for (int q = 0; q < 2; ++q) {
       if (q >= nc) break;
       const int c = c0 + q;
-      switch (spin) {
-        case 0: o[q] = hops_combine<DAG, 0>(half, c, ls); break;
-        case 1: o[q] = hops_combine<DAG, 1>(half, c, ls); break;
-        case 2: o[q] = hops_combine<DAG, 2>(half, c, ls); break;
-        default: o[q] = hops_combine<DAG, 3>(half, c, ls); break;
-      }
+      o[q] = hops_component<DAG>(half, spin, c, ls);
       if (EPI != EPI_PLAIN) {
         const R a = (R)e.a, bb = (R)e.b;
         if (e.y)
@@ -512,6 +526,119 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
     block_sum<2, 8>(v);
     if (threadIdx.x == 0) *(HMC_GLOBAL double*)e.alpha_out = v[0] / v[1];
   }
+}
+
+// Mhat on a lattice of at most kSmallSites half-lattice sites in one launch of
+// one block: sixteen wavefronts, one hop of 64 sites each as above, take the
+// odd sites and then, from LDS, the even ones (the odd field stays in the
+// arithmetic's precision).  The second hop's links and the addend are
+// requested before the first one's barriers (with its own loads they spill).  At this size a hop is one round of loads and its
+// launch costs more than it does: 4^4, FP64, 10.2 us in two launches, 7.1 in
+// one.  Twice the sites would need two steps per hop (4^3x8 12.9 us against
+// 10.0 in two launches).
+constexpr int kSmallThreads = 16 * 64;
+static_assert(kSmallSites == 2 * 64, "two groups of 64 sites per block");
+
+template <class SP, class LK, bool DAG>
+__global__ void __launch_bounds__(kSmallThreads) k_mhat_small(Lat g, const void* U, const void* in, void* out,
+                                                              double b) {
+  using R = typename SP::R;
+  __shared__ cx<R> half[2][8][6][64];
+  __shared__ cx<R> odd[12][kSmallSites];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = wave & 7, pair = wave >> 3;
+  const int spin = w & 3, c0 = w < 4 ? 0 : 2, nc = w < 4 ? 2 : 1;
+  const int s = 64 * pair + lane, back = w & 1;
+  const bool active = s < g.Vh;
+  bool wrap_o = false, wrap_e = false;
+  int sn_o = 0, sn_e = 0;
+  cx<R> psi[12], uh[6], y[2], o[2];
+  mat3<R> u;
+  if (active) {
+    sn_o = hop_neighbour(g, cb_site(g, 1, s), w, &wrap_o);
+    sn_e = hop_neighbour(g, cb_site(g, 0, s), w, &wrap_e);
+    SP::load(in, g.stride, sn_o, psi);
+    LK::raw_u(U, g.stride, w >> 1, 1 ^ back, back ? sn_o : s, u);
+    hop_half<LK, DAG>(g, U, w, 1 ^ back, back ? sn_o : s, wrap_o, psi, u, uh);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) half[pair][w][k][lane] = uh[k];
+    LK::raw_u(U, g.stride, w >> 1, back, back ? sn_e : s, u);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (q < nc) y[q] = SP::load_one(in, g.stride, s, 3 * spin + c0 + q);
+  }
+  __syncthreads();
+  if (active)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (q < nc) odd[3 * spin + c0 + q][s] = hops_component<DAG>(half[pair], spin, c0 + q, lane);
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) psi[k] = odd[k][sn_e];
+    hop_half<LK, DAG>(g, U, w, back, back ? sn_e : s, wrap_e, psi, u, uh);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) half[pair][w][k][lane] = uh[k];
+  }
+  __syncthreads();
+  if (active)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (q >= nc) break;
+      const R bb = (R)b;
+      o[q] = hops_component<DAG>(half[pair], spin, c0 + q, lane);
+      o[q] = {fma(bb, o[q].re, y[q].re), fma(bb, o[q].im, y[q].im)};
+      if constexpr (!SP::kScaled) SP::template store_one<false>(out, g.stride, s, 3 * spin + c0 + q, o[q]);
+    }
+  if constexpr (SP::kScaled) {  // the site's scale: its largest component
+    __shared__ float smax[16][64];
+    float m = 0.f;
+    if (active)
+      for (int q = 0; q < 2; ++q)
+        if (q < nc) m = fmaxf(m, fmaxf(fabsf((float)o[q].re), fabsf((float)o[q].im)));
+    smax[wave][lane] = m;
+    __syncthreads();
+    m = smax[8 * pair][lane];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) m = fmaxf(m, smax[8 * pair + q][lane]);
+    m = SP::live_scale(m);
+    const float inv = m > 0.f ? 1.f / m : 0.f;
+    if (active) {
+      if (w == 7) SP::template store_scale<false>(out, g.stride, s, m);
+      for (int q = 0; q < 2; ++q)
+        if (q < nc) SP::template store_one_scaled<false>(out, g.stride, s, 3 * spin + c0 + q, o[q], inv);
+    }
+  }
+}
+
+// out = in + b D_eo D_oe in (dagger: of D^dag) on at most kSmallSites sites.
+template <class SP, class LK>
+hipError_t launch_mhat_small_links(hmc_prec prec, int dagger, const LatArg& g, const void* U, const void* in, void* out,
+                                   double b, bool su3, hipStream_t st) {
+  if (g.Vh > kSmallSites) return hipErrorInvalidValue;
+  const int form = link_form_for(su3, dslash_link_form(g, prec));
+  const int lb = form == LINK_ROWCOL ? LkRowCol<LK>::kBytes : form == LINK_ROWS2 ? LkRows2<LK>::kBytes : LK::kBytes;
+  // the links of the two hops, the input as spinor and as addend, the output
+  const KernelEvents ev = timing_kernel_events(TK_DSLASH, (16.0 * LK::kBytes + 3 * SP::kBytes) * g.Vh,
+                                               (16.0 * lb + 3 * SP::kBytes) * g.Vh);
+  const Lat lat = to_lat(g);
+#define HMC_SMALL(LKF)                                                                                              \
+  do {                                                                                                              \
+    if (dagger)                                                                                                     \
+      hipExtLaunchKernelGGL((k_mhat_small<SP, LKF, true>), dim3(1), dim3(kSmallThreads), 0, st, ev.start, ev.stop,  \
+                            0, lat, U, in, out, b);                                                                 \
+    else                                                                                                            \
+      hipExtLaunchKernelGGL((k_mhat_small<SP, LKF, false>), dim3(1), dim3(kSmallThreads), 0, st, ev.start, ev.stop, \
+                            0, lat, U, in, out, b);                                                                 \
+  } while (0)
+  if (form == LINK_ROWCOL)
+    HMC_SMALL(LkRowCol<LK>);
+  else if (form == LINK_ROWS2)
+    HMC_SMALL(LkRows2<LK>);
+  else
+    HMC_SMALL(LK);
+#undef HMC_SMALL
+  return hipGetLastError();
 }
 
 template <class SP, class LK>

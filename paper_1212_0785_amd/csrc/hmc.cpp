@@ -346,6 +346,8 @@ hipError_t check_su3(Fields* F, hipStream_t st) {
 
 // Mhat (dag) on F64 half spinors: out = in - kappa^2 D_eo D_oe in.
 hipError_t mhat_f64(Fields* F, void* out, const void* in, int dag, double* partial, hipStream_t st) {
+  if (F->g.Vh <= kSmallSites && !partial)
+    return launch_mhat_small(HMC_F64, dag, F->g, F->U, in, out, -F->kappa * F->kappa, F->su3, st);
   hipError_t e = dslash_f64(F, F->t, in, 1, dag, EPI_PLAIN, nullptr, 0, 1, nullptr, nullptr, 0, st);
   if (e != hipSuccess) return e;
   return dslash_f64(F, out, F->t, 0, dag, partial ? EPI_AXPY_NORM : EPI_AXPY, in, 1.0, -F->kappa * F->kappa, partial,
@@ -629,6 +631,11 @@ hmc_status hmc_mhat(hmc_fields* f, void* out, const void* in, int32_t dagger, hm
     return HMC_OK;
   }
   HMC_CHECK_HIP(ensure_lowprec(F, prec, st));
+  if (F->g.Vh <= kSmallSites) {
+    HMC_CHECK_HIP(launch_mhat_small(prec, dagger ? 1 : 0, F->g, low_links(F, prec), in, out, -F->kappa * F->kappa,
+                                    F->su3, st));
+    return HMC_OK;
+  }
   DslashArgs d{};
   d.U = low_links(F, prec);
   d.su3 = F->su3;

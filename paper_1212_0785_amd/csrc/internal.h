@@ -167,6 +167,12 @@ enum Epilogue { EPI_PLAIN = 0, EPI_AXPY = 1, EPI_AXPY_NORM = 2, EPI_CG = 3 };
 hipError_t launch_dslash(hmc_prec prec, int dagger, int epi, const LatArg& g, int out_par, const DslashArgs* table,
                          int nbatch, const DslashArgs& one, hipStream_t st, int j = 0);
 
+// out = in + b D_eo D_oe in on even sites (dagger: of D^dag) in one launch, on
+// lattices of at most kSmallSites half-lattice sites.
+constexpr int kSmallSites = 128;
+hipError_t launch_mhat_small(hmc_prec prec, int dagger, const LatArg& g, const void* U, const void* in, void* out,
+                             double b, bool su3, hipStream_t st);
+
 // Layout conversion between canonical AoS complex128 (device) and SoA.
 // (the links' import also counts those that are not SU(3) to `tol`, one count
 // per block into bad[0 .. pack_gauge_blocks))

@@ -16,8 +16,9 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 BOUND = {0: 1e-14, 1: 1e-6, 2: 3e-3, 3: 2e-2}
-# half-lattice sites 8, 48, 192 (below one block), 320 and 1260 (ragged)
-HOP_L = [(2, 2, 2, 2), (2, 4, 6, 2), (4, 4, 4, 6), (8, 4, 2, 10), (10, 6, 14, 6)]
+# half-lattice sites 8, 48, 96 and 128 (Mhat in one launch), 192 (below one
+# block), 320 and 1260 (ragged)
+HOP_L = [(2, 2, 2, 2), (2, 4, 6, 2), (6, 2, 4, 4), (4, 4, 4, 4), (4, 4, 4, 6), (8, 4, 2, 10), (10, 6, 14, 6)]
 
 
 @pytest.fixture(scope="module")
@@ -49,9 +50,11 @@ def test_split_shapes(H, tmp_path, L, shape):
                     H.hmc_wilson_dslash(F, out, put_spinor(H, F, psi, 1 - par, prec=prec), par, dag, prec)
                     got = get_spinor(H, F, out, par, prec=prec)
                     assert rel(got, O.dslash(L, U, psi, par, dag)) < BOUND[prec], (form, prec, par, dag)
-            out = F.spinor(prec=prec)
-            H.hmc_mhat(F, out, put_spinor(H, F, psi, 0, prec=prec), 1, prec)
-            assert rel(get_spinor(H, F, out, 0, prec=prec), O.mhat(L, U, k, psi, 1)) < BOUND[prec], (form, prec)
+            for dag in (0, 1):
+                out = F.spinor(prec=prec)
+                H.hmc_mhat(F, out, put_spinor(H, F, psi, 0, prec=prec), dag, prec)
+                got = get_spinor(H, F, out, 0, prec=prec)
+                assert rel(got, O.mhat(L, U, k, psi, dag)) < BOUND[prec], (form, prec, dag)
         # the norm and residual epilogues
         b = put_spinor(H, F, psi, 0)
         x = F.spinor()
