@@ -270,25 +270,22 @@ __global__ void __launch_bounds__(kPlaqPairThreads) k_plaquette_pairs(Lat g, con
 }
 
 // Rows 0 and 1 of the links U_mu(x) and U_mu(x-mu) of a block's 64 sites,
-// parked in LDS by the site-blocked staple force: the wavefront of
-// direction mu needs U_nu(x) of the other three directions in its upper
-// staples (and its own link at the end) and U_nu(x-nu) in its lower ones,
-// which the block has then read from memory once instead of three times.
+// parked in LDS by the site-blocked staple force: both wavefronts of a plane
+// need the links U_mu(x), and the wavefront of direction mu the U_nu(x-nu) of
+// the other three in its lower staples.  Once the lower staples are done the
+// room of the second holds the forces of the six upper plaquettes.
 struct OwnLinks {
-  cx<double> m[4][6][64];     // U_mu(x)
-  cx<double> back[4][6][64];  // U_mu(x - mu)
+  cx<double> m[4][6][64];  // U_mu(x)
+  union {
+    cx<double> back[4][6][64];  // U_mu(x - mu)
+    double up[6][8][64];        // i c TA(plaquette), by plane
+  };
 };
 
-__device__ __forceinline__ mat3<double> own_link(const OwnLinks& o, int mu, int lane) {
+__device__ __forceinline__ mat3<double> lds_link(const cx<double> (*m)[64], int lane) {
   mat3<double> u;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) u.m[k] = o.m[mu][k][lane];
-  return u;
-}
-__device__ __forceinline__ mat3<double> back_link(const OwnLinks& o, int mu, int lane) {
-  mat3<double> u;
-#pragma unroll
-  for (int k = 0; k < 6; ++k) u.m[k] = o.back[mu][k][lane];
+  for (int k = 0; k < 6; ++k) u.m[k] = m[k][lane];
   return u;
 }
 
@@ -310,65 +307,61 @@ __device__ __forceinline__ mat3<double> slink2(const Lat& g, const void* U, int 
     return link2<LK>(g, U, mu, st);
 }
 
-// par: the parity of x (used where OWN: the site-blocked walk)
+// A += (U_mu(x-nu) U_nu(x+mu-nu))^dag U_nu(x-nu), the lower staple; the last
+// link from LDS where OWN.  par: the parity of x (used where OWN).
 template <class LK, int MU, int NU, bool OWN>
-__device__ __forceinline__ void add_staples_su3(const Lat& g, const void* U, Site x, Site xm, mat3<double>& A,
-                                                const OwnLinks* own, int lane, int par) {
-  const int po = par ^ 1;
+__device__ __forceinline__ void add_lower_su3(const Lat& g, const void* U, Site x, Site xm, mat3<double>& A,
+                                              const OwnLinks* own, int lane, int par) {
+  chain_sites(x, xm, A);
+  Site xmn = shift<NU, -1>(g, xm), xn = shift<NU, -1>(g, x);
+  mat3<double> H;
+  mul_r01(slink2<LK, OWN>(g, U, MU, xn, par ^ 1), slink<LK, OWN>(g, U, NU, xmn, par), H);
+  third_row(H);
+  chain_site(xn, H);
+  mat3<double> G;
+  if constexpr (OWN)
+    G = lds_link(own->back[NU], lane);
+  else
+    G = link2<LK>(g, U, NU, xn);
+  G.m[6] = conj(G.m[1] * G.m[5] - G.m[2] * G.m[4]);  // row 2, columns 0 and 1
+  G.m[7] = conj(G.m[2] * G.m[3] - G.m[0] * G.m[5]);
+  mat3<double> S;
+  mul_c01_dn(H, G, S);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    A.m[3 * i] = A.m[3 * i] + S.m[3 * i];
+    A.m[3 * i + 1] = A.m[3 * i + 1] + S.m[3 * i + 1];
+  }
+  A.m[2] = acc_conj_cross(A.m[2], S.m[3], S.m[7], S.m[6], S.m[4]);
+  A.m[5] = acc_conj_cross(A.m[5], S.m[6], S.m[1], S.m[0], S.m[7]);
+  A.m[8] = acc_conj_cross(A.m[8], S.m[0], S.m[4], S.m[3], S.m[1]);
+}
+
+template <class LK, int MU, int NU>
+__device__ __forceinline__ void add_staples_su3(const Lat& g, const void* U, Site x, Site xm, mat3<double>& A) {
   chain_sites(x, xm, A);
   {
     // upper: U_nu(x+mu) (U_nu(x) U_mu(x+nu))^dag
     Site xn = shift<NU, +1>(g, x);
-    mat3<double> C;
-    if constexpr (OWN)
-      C = own_link(*own, NU, lane);
-    else
-      C = link2<LK>(g, U, NU, x);
     mat3<double> D;
-    mul_r01(C, slink<LK, OWN>(g, U, MU, xn, po), D);
+    mul_r01(link2<LK>(g, U, NU, x), link<LK>(g, U, MU, xn), D);
     third_row(D);
     chain_site(xm, D);
     mat3<double> S;
-    mul_r01_nd(slink2<LK, OWN>(g, U, NU, xm, po), D, S);
+    mul_r01_nd(link2<LK>(g, U, NU, xm), D, S);
 #pragma unroll
     for (int k = 0; k < 6; ++k) A.m[k] = A.m[k] + S.m[k];
     A.m[6] = acc_conj_cross(A.m[6], S.m[1], S.m[5], S.m[2], S.m[4]);
     A.m[7] = acc_conj_cross(A.m[7], S.m[2], S.m[3], S.m[0], S.m[5]);
     A.m[8] = acc_conj_cross(A.m[8], S.m[0], S.m[4], S.m[1], S.m[3]);
   }
-  chain_sites(x, xm, A);
-  {
-    // lower: (U_mu(x-nu) U_nu(x+mu-nu))^dag U_nu(x-nu)
-    Site xmn = shift<NU, -1>(g, xm), xn = shift<NU, -1>(g, x);
-    mat3<double> H;
-    mul_r01(slink2<LK, OWN>(g, U, MU, xn, po), slink<LK, OWN>(g, U, NU, xmn, par), H);
-    third_row(H);
-    chain_site(xn, H);
-    mat3<double> G;
-    if constexpr (OWN)
-      G = back_link(*own, NU, lane);
-    else
-      G = link2<LK>(g, U, NU, xn);
-    G.m[6] = conj(G.m[1] * G.m[5] - G.m[2] * G.m[4]);  // row 2, columns 0 and 1
-    G.m[7] = conj(G.m[2] * G.m[3] - G.m[0] * G.m[5]);
-    mat3<double> S;
-    mul_c01_dn(H, G, S);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      A.m[3 * i] = A.m[3 * i] + S.m[3 * i];
-      A.m[3 * i + 1] = A.m[3 * i + 1] + S.m[3 * i + 1];
-    }
-    A.m[2] = acc_conj_cross(A.m[2], S.m[3], S.m[7], S.m[6], S.m[4]);
-    A.m[5] = acc_conj_cross(A.m[5], S.m[6], S.m[1], S.m[0], S.m[7]);
-    A.m[8] = acc_conj_cross(A.m[8], S.m[0], S.m[4], S.m[3], S.m[1]);
-  }
+  add_lower_su3<LK, MU, NU, false>(g, U, x, xm, A, nullptr, 0, 0);
 }
 
-template <class LK, int MU, int NU, bool OWN = false>
-__device__ __forceinline__ void add_staples(const Lat& g, const void* U, Site x, Site xm, mat3<double>& A,
-                                            const OwnLinks* own = nullptr, int lane = 0, int par = 0) {
+template <class LK, int MU, int NU>
+__device__ __forceinline__ void add_staples(const Lat& g, const void* U, Site x, Site xm, mat3<double>& A) {
   if constexpr (CompactLinks<LK>::value) {
-    add_staples_su3<LK, MU, NU, OWN>(g, U, x, xm, A, own, lane, par);
+    add_staples_su3<LK, MU, NU>(g, U, x, xm, A);
     return;
   }
   chain_sites(x, xm, A);
@@ -390,41 +383,32 @@ __device__ __forceinline__ void add_staples(const Lat& g, const void* U, Site x,
 
 // P_mu(x) += (i coef beta / 12) TA(U_mu(x) A), A the staple sum: with
 // F = -(i beta / 12) TA(W) this is P <- P - coef F.
-template <class LK, int MU, bool OWN = false, bool NT = false>
+template <class LK, int MU>
 __device__ __forceinline__ void gauge_force_finish(const Lat& g, const void* U, double* P, double coef_beta, int par,
-                                                   int s, const mat3<double>& A, const OwnLinks* own = nullptr,
-                                                   int lane = 0) {
-  mat3<double> u;
-  if constexpr (OWN) {
-    u = own_link(*own, MU, lane);
-    third_row(u);
-  } else {
-    u = LK::load(U, g.stride, MU, par, s);
-  }
-  mat3<double> W = mmul(u, A);
+                                                   int s, const mat3<double>& A) {
+  mat3<double> W = mmul(LK::load(U, g.stride, MU, par, s), A);
   double f[8], c[8];
   i_ta_compact(W, coef_beta / 12.0, f);
-  // NT: non-temporal momentum accesses (each read and written once)
   double* pm = P + (size_t)(MU * 2 + par) * 8 * g.stride;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) c[k] = gld_link<double, NT>(pm, k * g.stride + s);
+  for (int k = 0; k < 8; ++k) c[k] = pm[k * g.stride + s];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) gput<NT>(pm, k * g.stride + s, c[k] + f[k]);
+  for (int k = 0; k < 8; ++k) pm[k * g.stride + s] = c[k] + f[k];
 }
 
-template <class LK, int MU, bool OWN = false, bool NT = false>
+template <class LK, int MU>
 __device__ __forceinline__ void gauge_force_link(const Lat& g, const void* U, double* P, double coef_beta, int par,
-                                                 int s, const OwnLinks* own = nullptr, int lane = 0) {
+                                                 int s) {
   Site x = cb_site(g, par, s);
   Site xm = shift<MU, +1>(g, x);
   mat3<double> A;
 #pragma unroll
   for (int k = 0; k < 9; ++k) A.m[k] = {0.0, 0.0};
-  if (MU != 0) add_staples<LK, MU, 0, OWN>(g, U, x, xm, A, own, lane, par);
-  if (MU != 1) add_staples<LK, MU, 1, OWN>(g, U, x, xm, A, own, lane, par);
-  if (MU != 2) add_staples<LK, MU, 2, OWN>(g, U, x, xm, A, own, lane, par);
-  if (MU != 3) add_staples<LK, MU, 3, OWN>(g, U, x, xm, A, own, lane, par);
-  gauge_force_finish<LK, MU, OWN, NT>(g, U, P, coef_beta, par, s, A, own, lane);
+  if (MU != 0) add_staples<LK, MU, 0>(g, U, x, xm, A);
+  if (MU != 1) add_staples<LK, MU, 1>(g, U, x, xm, A);
+  if (MU != 2) add_staples<LK, MU, 2>(g, U, x, xm, A);
+  if (MU != 3) add_staples<LK, MU, 3>(g, U, x, xm, A);
+  gauge_force_finish<LK, MU>(g, U, P, coef_beta, par, s, A);
 }
 
 template <class LK>
@@ -440,47 +424,135 @@ __global__ void __launch_bounds__(kBlock) k_gauge_force(Lat g, const void* U, do
   }
 }
 
+// i c TA of the plaquette p = U_mu(x) U_nu(x+mu) (U_nu(x) U_mu(x+nu))^dag of
+// a plane, into LDS.  p is the upper staple's share of W_mu(x), p^dag its
+// share of W_nu(x), and TA(p^dag) = -TA(p): one product serves both links.
+template <class LK, int MU, int NU>
+__device__ __forceinline__ void upper_plane(const Lat& g, const void* U, Site& x, double c, int par, int lane,
+                                            OwnLinks& own) {
+  constexpr int plane = MU == 0 ? NU - 1 : MU + NU;  // 01 02 03 12 13 23
+  mat3<double> D, E, p;
+  mul_r01(lds_link(own.m[NU], lane), slink<LK, true>(g, U, MU, shift<NU, +1>(g, x), par ^ 1), E);
+  mul_r01(lds_link(own.m[MU], lane), slink<LK, true>(g, U, NU, shift<MU, +1>(g, x), par ^ 1), D);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(D.m[k].re), "+v"(D.m[k].im));
+  third_row(E);
+  mul_r01_nd(D, E, p);
+  third_row(p);
+  double f[8];
+  i_ta_compact(p, c, f);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(f[k]));
+  asm volatile("" : "+v"(x.lex) : : "memory");  // the next plane's loads after this one
+#pragma unroll
+  for (int k = 0; k < 8; ++k) own.up[plane][k][lane] = f[k];
+}
+
+// The part of direction MU: its three lower staples, the upper plaquettes of
+// one or two planes, and the momenta of its links.  Every work-item of the
+// block runs it (sites past the end on site 0, storing nothing) and reaches
+// both barriers.
+template <class LK, int MU, bool NT>
+__device__ __forceinline__ void gauge_force_dir(const Lat& g, const void* U, double* P, double coef_beta, int par,
+                                                int s, bool on, OwnLinks& own, int lane) {
+  Site x = cb_site(g, par, s);
+  const double c = coef_beta / 12.0;
+  double f[8];
+  {
+    const Site xm = shift<MU, +1>(g, x);
+    mat3<double> A;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) A.m[k] = {0.0, 0.0};
+    if (MU != 0) add_lower_su3<LK, MU, 0, true>(g, U, x, xm, A, &own, lane, par);
+    if (MU != 1) add_lower_su3<LK, MU, 1, true>(g, U, x, xm, A, &own, lane, par);
+    if (MU != 2) add_lower_su3<LK, MU, 2, true>(g, U, x, xm, A, &own, lane, par);
+    if (MU != 3) add_lower_su3<LK, MU, 3, true>(g, U, x, xm, A, &own, lane, par);
+    mat3<double> u = lds_link(own.m[MU], lane);
+    third_row(u);
+    i_ta_compact(mmul(u, A), c, f);
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(f[k]));
+  asm volatile("" : "+v"(x.lex) : : "memory");
+  __syncthreads();
+  if constexpr (MU == 0) {
+    upper_plane<LK, 0, 1>(g, U, x, c, par, lane, own);
+    upper_plane<LK, 0, 2>(g, U, x, c, par, lane, own);
+  } else if constexpr (MU == 3) {
+    upper_plane<LK, 0, 3>(g, U, x, c, par, lane, own);
+    upper_plane<LK, 1, 3>(g, U, x, c, par, lane, own);
+  } else
+    upper_plane<LK, MU, MU + 1>(g, U, x, c, par, lane, own);
+  // NT: non-temporal momentum accesses (each read and written once)
+  double* pm = P + (size_t)(MU * 2 + par) * 8 * g.stride;
+  asm volatile("" : "+v"(s) : : "memory");
+  double q[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) q[k] = gld_link<double, NT>(pm, k * g.stride + s);
+  __syncthreads();
+  if (!on) return;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    double t = f[k];
+    if constexpr (MU == 0)
+      t += own.up[0][k][lane] + own.up[1][k][lane] + own.up[2][k][lane];
+    else if constexpr (MU == 1)
+      t += own.up[3][k][lane] + own.up[4][k][lane] - own.up[0][k][lane];
+    else if constexpr (MU == 2)
+      t += own.up[5][k][lane] - own.up[1][k][lane] - own.up[3][k][lane];
+    else
+      t -= own.up[2][k][lane] + own.up[4][k][lane] + own.up[5][k][lane];
+    gput<NT>(pm, k * g.stride + s, q[k] + t);
+  }
+}
+
 // Site-blocked form: a block of four wavefronts covers 64 sites of one
-// parity, wavefront w the links U_w of those sites (walk_site with the
-// block as the walk unit).  With compact (SU(3)) links the block first
-// parks rows 0 and 1 of its 256 own links and of the 256 links U_mu(x-mu)
-// in LDS (48 KB), which the wavefronts read for their staples and for the
-// final product instead of loading each three times.
+// parity, a wavefront the links of one direction (walk_site with the block
+// as the walk unit).  With compact (SU(3)) links the block first parks rows
+// 0 and 1 of its 256 own links and of the 256 links U_mu(x-mu) in LDS
+// (48 KB).  The kernel is bound by its FP64 instructions (58% of the cycles
+// of 24^3x48) and the waits for the links that feed them, so each upper
+// plaquette of the block's sites is formed once for both of its links: two
+// rows a link, 24^3x48 271 -> 244 us, 48^3x96 4.83 -> 4.05 ms (there also the
+// change from ten reals a link).  Two of the directions take two of the six
+// planes: which wavefronts (SIMDs) have them changes from block to block.
+// 24 KB and 128 registers, four blocks on a compute unit, lose 3%.
 template <class LK, bool NT>
 __global__ void __launch_bounds__(kBlock) k_gauge_force_sites(Lat g, const void* U, double* P, double coef_beta) {
   int par, s;
   walk_site(g, blockIdx.x & 7, walk_unit(g, 1), &par, &s);
   par = __builtin_amdgcn_readfirstlane(par);  // one parity per walk unit
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // the wavefront (direction), as a scalar
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (CompactLinks<LK>::value) {
-    // each wavefront parks rows 0 and 1 of its own links; every work-item
-    // reaches the barrier
     __shared__ OwnLinks own;
     const int lane = threadIdx.x & 63;
-    if (s < g.Vh) {
+    const bool on = s < g.Vh;
+    if (!on) s = 0;
+    const int d = (w + (blockIdx.x >> 3) + (blockIdx.x >> 8)) & 3;
+    {
       const Site x = cb_site(g, par, s);
-      const mat3<double> u = LK::load2_u(U, g.stride, w, par, s);
+      const mat3<double> u = LK::load2_u(U, g.stride, d, par, s);
       Site xb;
-      switch (w) {
+      switch (d) {
         case 0: xb = shift<0, -1>(g, x); break;
         case 1: xb = shift<1, -1>(g, x); break;
         case 2: xb = shift<2, -1>(g, x); break;
         default: xb = shift<3, -1>(g, x); break;
       }
-      const mat3<double> ub = LK::load2_u(U, g.stride, w, par ^ 1, xb.lex >> 1);
+      const mat3<double> ub = LK::load2_u(U, g.stride, d, par ^ 1, xb.lex >> 1);
 #pragma unroll
       for (int k = 0; k < 6; ++k) {
-        own.m[w][k][lane] = u.m[k];
-        own.back[w][k][lane] = ub.m[k];
+        own.m[d][k][lane] = u.m[k];
+        own.back[d][k][lane] = ub.m[k];
       }
     }
     __syncthreads();
-    if (s >= g.Vh) return;
-    switch (w) {
-      case 0: gauge_force_link<LK, 0, true, NT>(g, U, P, coef_beta, par, s, &own, lane); break;
-      case 1: gauge_force_link<LK, 1, true, NT>(g, U, P, coef_beta, par, s, &own, lane); break;
-      case 2: gauge_force_link<LK, 2, true, NT>(g, U, P, coef_beta, par, s, &own, lane); break;
-      default: gauge_force_link<LK, 3, true, NT>(g, U, P, coef_beta, par, s, &own, lane); break;
+    // d is uniform over a wavefront; each case holds the same two barriers
+    switch (d) {
+      case 0: gauge_force_dir<LK, 0, NT>(g, U, P, coef_beta, par, s, on, own, lane); break;
+      case 1: gauge_force_dir<LK, 1, NT>(g, U, P, coef_beta, par, s, on, own, lane); break;
+      case 2: gauge_force_dir<LK, 2, NT>(g, U, P, coef_beta, par, s, on, own, lane); break;
+      default: gauge_force_dir<LK, 3, NT>(g, U, P, coef_beta, par, s, on, own, lane); break;
     }
     return;
   }

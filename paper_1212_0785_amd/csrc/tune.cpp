@@ -249,8 +249,10 @@ int staple_link_form(const LatArg& g) {
   if (forced_link_form() > 0) return forced_link_form();
   const int t = tune_lookup(g.L, TUNE_GFORCE_LINKS, HMC_F64);
   if (t > 0) return t;
-  // measured on MI355X: faster at 16^3x32 and 48^3x96
-  return LINK_ROWCOL;
+  // measured on MI355X, ten reals a link against twelve: 18x10x14x26 33.5 and
+  // 27.3 us, 20^3x40 145 and 117, 32^3x64 965 and 809, 48^3x96 4.83 and
+  // 4.05 ms (the kernel waits for its arithmetic before its bytes)
+  return LINK_ROWS2;
 }
 
 int dslash_shape(const LatArg& g, hmc_prec prec) {
