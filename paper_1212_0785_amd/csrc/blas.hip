@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "device.h"
 #include "internal.h"
@@ -208,12 +209,58 @@ __global__ void __launch_bounds__(kBlock) k_cg_init(Lat g, const double2* b, dou
 // or the single entry passed by value.  Chosen at compile time, so the
 // by-value entry is read in place from the kernel arguments (a run-time
 // choice copies the struct to per-lane scratch memory).
+// Arguments of the two launches below: single entries in at most 112 bytes and
+// the block count inside, for which a launch costs the host 2.9 us instead of
+// 3.7 (as the Dslash's).
+struct CgOne {
+  int Vh, label;  // (label without the base)
+  void *x, *p, *r;
+  const void* qs;  // q (update) or s (p-update)
+  double* pp;
+  int pp1;    // pp[1] - pp[0]
+  int flags;  // blocks per XCD, mixed, cgls
+  double *pq, *pr;
+  int n_pp, n_pq, n_pr, max_iters;
+  SolverState* state;
+  double delta2;
+  void* x64;
+
+  CgOne(int Vh_, int blocks, const CgArgs& a, const void* qs_, int j)
+      : Vh(Vh_), label(a.iter0 + j), x(a.x), p(a.p), r(a.r), qs(qs_), pp(a.pp[0]), pp1((int)(a.pp[1] - a.pp[0])),
+        flags((blocks >> 3) << 2 | (a.mixed ? 2 : 0) | (a.cgls ? 1 : 0)), pq(a.pq), pr(a.pr), n_pp(a.n_pp),
+        n_pq(a.n_pq), n_pr(a.n_pr), max_iters(a.max_iters), state(a.state), delta2(a.delta2), x64(a.x64) {}
+  // What the launch relies on: both partial buffers are cut from one.
+  static bool holds(const CgArgs& a) {
+    const long long d = a.pp[1] - a.pp[0];
+    return d == (int)d;
+  }
+};
+static_assert(sizeof(CgOne) <= 112, "launch arguments");
+struct CgBatch {  // blockIdx.y selects an entry of `table`
+  int Vh, blocks;
+  const CgArgs* table;
+  int j;
+};
 template <bool BATCH>
-__device__ __forceinline__ const CgArgs& cg_args(const CgArgs* table, const CgArgs& one) {
-  if constexpr (BATCH)
-    return table[blockIdx.y];
-  else
-    return one;
+using CgParam = std::conditional_t<BATCH, CgBatch, CgOne>;
+
+// The entry's arguments, its label without the base and the blocks per XCD.
+__device__ __forceinline__ CgArgs cg_args(const CgOne& h, int* label, int* nbx) {
+  CgArgs a;
+  a.x = h.x, a.p = h.p, a.r = h.r, a.q = a.s = h.qs;
+  a.pp[0] = h.pp, a.pp[1] = h.pp + h.pp1, a.pq = h.pq, a.pr = h.pr;
+  a.n_pp = h.n_pp, a.n_pq = h.n_pq, a.n_pr = h.n_pr, a.max_iters = h.max_iters;
+  a.state = h.state, a.delta2 = h.delta2, a.x64 = h.x64;
+  a.cgls = h.flags & 1, a.mixed = h.flags >> 1 & 1;
+  *label = h.label;
+  *nbx = h.flags >> 2;
+  return a;
+}
+__device__ __forceinline__ const CgArgs& cg_args(const CgBatch& h, int* label, int* nbx) {
+  const CgArgs& a = h.table[blockIdx.y];
+  *label = a.iter0 + h.j;
+  *nbx = h.blocks >> 3;
+  return a;
 }
 
 // One solver iteration with label k = iter0 + j; cur = k & 1, nxt = cur ^ 1.
@@ -233,7 +280,7 @@ __device__ __forceinline__ const CgArgs& cg_args(const CgArgs* table, const CgAr
 // components 3 part .. 3 part + 2 of site s.  For a storage with a per-site
 // scale, which needs all twelve components, the four are the wavefronts of one
 // block, which exchange their largest components through LDS.  XCD x (hardware blocks b with b % 8 == x;
-// gridDim.x is a multiple of 8) takes the sites [x Vh / 8, (x + 1) Vh / 8),
+// their number is a multiple of 8) takes the sites [x Vh / 8, (x + 1) Vh / 8),
 // the range the Dslash's XCD-aware block order gives the same XCD, so the
 // vectors stay in the L2 of the XCD that reads them next.  The first element's
 // loads depend on no sum and are issued before anything is waited for.
@@ -244,11 +291,11 @@ struct VecRange {
 // w of a block has part w of 64 sites, so i runs over groups of 64 sites times
 // four parts, and all four wavefronts of a block make the same steps.
 template <bool SCALED>
-__device__ __forceinline__ VecRange vec_range(const Lat& g) {
+__device__ __forceinline__ VecRange vec_range(int Vh, int nbx) {
   VecRange v;
-  const int xcd = blockIdx.x & 7, nbx = gridDim.x >> 3;
-  v.lo = (int)((long long)g.Vh * xcd / 8);
-  v.nsx = (int)((long long)g.Vh * (xcd + 1) / 8) - v.lo;
+  const int xcd = blockIdx.x & 7;
+  v.lo = (int)((long long)Vh * xcd / 8);
+  v.nsx = (int)((long long)Vh * (xcd + 1) / 8) - v.lo;
   v.nwork = SCALED ? (v.nsx + 63) / 64 * kBlock : v.nsx * 4;
   v.first = (blockIdx.x >> 3) * kBlock + threadIdx.x;
   v.step = nbx * kBlock;
@@ -295,20 +342,22 @@ __device__ __forceinline__ void store_components(void* v, int stride, int s, int
 }
 
 template <class SP, bool BATCH>
-__global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table, CgArgs one, int j) {
+__global__ void __launch_bounds__(kBlock) k_cg_update(CgParam<BATCH> h) {
   using R = typename SP::R;
   constexpr int NC = 3;
-  const CgArgs& a = cg_args<BATCH>(table, one);
-  const VecRange w = vec_range<SP::kScaled>(g);
+  int label, nbx;
+  const CgArgs& a = cg_args(h, &label, &nbx);
+  const int Vh = h.Vh;
+  const VecRange w = vec_range<SP::kScaled>(Vh, nbx);
   cx<R> q[NC] = {}, r[NC] = {};  // (zero where a work-item has no site)
   auto load = [&](int i) {
     int part;
     const int s = vec_site<SP::kScaled>(w, i, &part);
     if (SP::kScaled && s < 0) return;
-    load_components<SP>(a.q, g.stride, s, part, q);
-    load_components<SP>(a.r, g.stride, s, part, r);
+    load_components<SP>(a.q, Vh, s, part, q);
+    load_components<SP>(a.r, Vh, s, part, r);
   };
-  const int k = a.iter0 + a.state->base + j;
+  const int k = label + a.state->base;
   if (a.mixed) {  // many launches of a mixed chunk are past its stop: they leave before they load
     if (k >= a.state->stop_at) return;
     asm volatile("" ::: "memory");
@@ -317,7 +366,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table
   const int stop = a.state->stop_at;
   asm volatile("" ::: "memory");  // the loads above stay above
   if (k >= stop) return;
-  const double* part[2] = {a.pp[k & 1], a.pq};
+  const double* part[2] = {k & 1 ? a.pp[1] : a.pp[0], a.pq};
   const int n[2] = {a.n_pp, a.n_pq};
   double sums[2];
   sum_partials_n<kBlock / 64, 2>(part, n, sums);
@@ -336,7 +385,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table
         r[m].im = fma(-al, q[m].im, r[m].im);
         v[0] += (double)r[m].re * r[m].re + (double)r[m].im * r[m].im;
       }
-    store_components<SP>(a.r, g.stride, s, part, r);
+    store_components<SP>(a.r, Vh, s, part, r);
   }
   block_sum<1>(v);
   if (threadIdx.x == 0) a.pr[blockIdx.x] = v[0];
@@ -349,14 +398,16 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Lat g, const CgArgs* table
 // Every input of an element is loaded before any output is stored (x, p and r
 // are distinct arrays), so a work-item makes one round trip to memory.
 template <class SP, class SX, bool BATCH>
-__global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* table, CgArgs one, int j) {
-  const CgArgs& a = cg_args<BATCH>(table, one);
+__global__ void __launch_bounds__(kBlock) k_cg_pupdate(CgParam<BATCH> h) {
+  int label, nbx;
+  const CgArgs& a = cg_args(h, &label, &nbx);
+  const int Vh = h.Vh;
   SolverState* stt = a.state;
   using R = typename SP::R;
   using XR = typename SX::R;
   constexpr int NC = 3;  // components per work-item
   const void* src = a.cgls ? a.s : a.r;
-  const VecRange w = vec_range<SP::kScaled>(g);
+  const VecRange w = vec_range<SP::kScaled>(Vh, nbx);
   const int nwork = w.nwork, i0 = w.first;
   cx<R> p[NC] = {}, q[NC] = {};  // (zero where a work-item has no site)
   cx<XR> x[NC];
@@ -364,14 +415,14 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
     int part;
     const int s = vec_site<SP::kScaled>(w, i, &part);
     if (SP::kScaled && s < 0) return;
-    load_components<SP>(a.p, g.stride, s, part, p);
-    load_components<SX>(a.x, g.stride, s, part, x);
-    load_components<SP>(src, g.stride, s, part, q);
+    load_components<SP>(a.p, Vh, s, part, p);
+    load_components<SX>(a.x, Vh, s, part, x);
+    load_components<SP>(src, Vh, s, part, q);
   };
   // the state as the launch found it, read once (block 0 writes iters, last,
   // rr, the other parity's sum_pp, stop_at beyond this label, and maxrr only to
   // a value that leaves the decision below as it is)
-  const int k = a.iter0 + stt->base + j;
+  const int k = label + stt->base;
   if (a.mixed) {  // many launches of a mixed chunk are past its stop: they leave before they load
     if (k >= stt->stop_at) return;
     asm volatile("" ::: "memory");
@@ -383,6 +434,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
   asm volatile("" ::: "memory");  // the loads above stay above
   if (k >= stop) return;
   const int cur = k & 1, nxt = cur ^ 1;
+  const double *pp_cur = cur ? a.pp[1] : a.pp[0], *pp_nxt = cur ? a.pp[0] : a.pp[1];
   // the sums of this step in one block reduction (same order, hence the same
   // bits, in every block).  sum(pp[cur]) is the previous iteration's
   // sum(pp[nxt]), which its block 0 left in the state: it is summed again only
@@ -401,7 +453,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = base + u * kBlock;
-        t0[u] = i < a.n_pp ? a.pp[nxt][i] : 0.0;
+        t0[u] = i < a.n_pp ? pp_nxt[i] : 0.0;
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) v[0] += t0[u];
@@ -409,7 +461,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int i = base + u * kBlock;
-          v[1] += i < a.n_pp ? a.pp[cur][i] : 0.0;
+          v[1] += i < a.n_pp ? pp_cur[i] : 0.0;
         }
     }
     if (a.cgls)
@@ -483,13 +535,13 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
       if (fold) {
 #pragma unroll
         for (int m = 0; m < NC; ++m) {
-          double2* h = (double2*)a.x64 + (size_t)(NC * part + m) * g.stride + s;
+          double2* h = (double2*)a.x64 + (size_t)(NC * part + m) * Vh + s;
           const double2 v = *h;
           *h = make_double2(v.x + (double)x[m].re, v.y + (double)x[m].im);
           x[m] = {(XR)0, (XR)0};
         }
       }
-      store_components<SX>(a.x, g.stride, s, part, x);
+      store_components<SX>(a.x, Vh, s, part, x);
     }
     if (p_done) continue;
     if (on)
@@ -498,7 +550,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(Lat g, const CgArgs* tabl
         p[m].re = fma(beta, p[m].re, q[m].re);
         p[m].im = fma(beta, p[m].im, q[m].im);
       }
-    store_components<SP>(a.p, g.stride, s, part, p);
+    store_components<SP>(a.p, Vh, s, part, p);
   }
 }
 
@@ -763,12 +815,13 @@ hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, con
                             hipStream_t st) {
   // r -= alpha q: q read, r read + written
   TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, false, 3) * g.Vh * nbatch);
+  if (g.stride != g.Vh || (!table && !CgOne::holds(a))) return hipErrorInvalidValue;
   const dim3 grid(cg_vec_blocks(g.Vh), nbatch), block(kBlock);
   auto go = [&](auto kernel_single, auto kernel_batch) {
     if (table)
-      hipLaunchKernelGGL(kernel_batch, grid, block, 0, st, to_lat(g), table, a, j);
+      hipLaunchKernelGGL(kernel_batch, grid, block, 0, st, CgBatch{g.Vh, (int)grid.x, table, j});
     else
-      hipLaunchKernelGGL(kernel_single, grid, block, 0, st, to_lat(g), table, a, j);
+      hipLaunchKernelGGL(kernel_single, grid, block, 0, st, CgOne(g.Vh, grid.x, a, a.q, j));
   };
   switch (prec) {
     case HMC_F64: go(k_cg_update<SpF64, false>, k_cg_update<SpF64, true>); break;
@@ -783,12 +836,13 @@ hipError_t launch_cg_pupdate(const LatArg& g, hmc_prec prec, const CgArgs& a, co
                              hipStream_t st) {
   // x += alpha p, p = r + beta p: x and p read + written, r read
   TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, true, 3) * g.Vh * nbatch);
+  if (g.stride != g.Vh || (!table && !CgOne::holds(a))) return hipErrorInvalidValue;
   const dim3 grid(cg_vec_blocks(g.Vh), nbatch), block(kBlock);
   auto go = [&](auto kernel_single, auto kernel_batch) {
     if (table)
-      hipLaunchKernelGGL(kernel_batch, grid, block, 0, st, to_lat(g), table, a, j);
+      hipLaunchKernelGGL(kernel_batch, grid, block, 0, st, CgBatch{g.Vh, (int)grid.x, table, j});
     else
-      hipLaunchKernelGGL(kernel_single, grid, block, 0, st, to_lat(g), table, a, j);
+      hipLaunchKernelGGL(kernel_single, grid, block, 0, st, CgOne(g.Vh, grid.x, a, a.s, j));
   };
   switch (prec) {
     case HMC_F64: go(k_cg_pupdate<SpF64, SpF64, false>, k_cg_pupdate<SpF64, SpF64, true>); break;

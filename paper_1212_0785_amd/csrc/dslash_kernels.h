@@ -23,6 +23,7 @@
 #include <hip/hip_ext.h>
 
 #include <climits>
+#include <type_traits>
 
 #include "device.h"
 #include "internal.h"
@@ -119,7 +120,8 @@ __device__ __forceinline__ void alpha_prologue(const DslashArgs& e, int label) {
 __device__ __forceinline__ void put_partial(const DslashArgs& e, int label, int b, double v) {
   if (threadIdx.x != 0) return;
   if (e.partial) ((HMC_GLOBAL double*)e.partial)[b] = v;
-  if (e.partial_pp[0]) ((HMC_GLOBAL double*)e.partial_pp[e.partial ? 0 : (label + 1) & 1])[b] = v;
+  if (e.partial_pp[0])
+    ((HMC_GLOBAL double*)(e.partial || (label & 1) ? e.partial_pp[0] : e.partial_pp[1]))[b] = v;
 }
 
 // BATCH: blockIdx.y selects an entry of `table` (same-volume requests share
@@ -391,17 +393,117 @@ __device__ __forceinline__ cx<R> hops_component(const cx<R> (*half)[6][64], int 
 constexpr int kHopThreads = 8 * 64;
 constexpr int kAlphaAhead = 2;  // partial sums per work-item requested ahead (1024 in all, a 2^16-site launch's)
 
+// Arguments of one launch.  The host writes a kernel's arguments on the
+// caller's thread: 2.9 us a launch with at most 112 bytes of them and no use of
+// the grid's extent (which adds 256 bytes), 3.7 us with more, and the launches
+// are what a solve on a small lattice waits for (8^4, FP32: 650 of them).  So a
+// single entry travels without what the kernel can derive (number of sites and
+// blocks, the stop's neighbour in the solver state) or its epilogue does not
+// read; every addend enters with the factor 1, and EPI_CG works in place.
+template <int EPI>
+struct HopEpilogue {  // EPI_PLAIN
+  const double *alpha_pp[2], *alpha_den;
+  double* alpha_out;
+  int alpha_n_pp, alpha_n_den;
+  HopEpilogue(const DslashArgs& d)
+      : alpha_pp{d.alpha_pp[0], d.alpha_pp[1]}, alpha_den(d.alpha_den), alpha_out(d.alpha_out),
+        alpha_n_pp(d.alpha_n_pp), alpha_n_den(d.alpha_n_den) {}
+  __device__ void expand(DslashArgs& d) const {
+    d.alpha_pp[0] = alpha_pp[0], d.alpha_pp[1] = alpha_pp[1], d.alpha_den = alpha_den, d.alpha_out = alpha_out;
+    d.alpha_n_pp = alpha_n_pp, d.alpha_n_den = alpha_n_den;
+  }
+};
+template <>
+struct HopEpilogue<EPI_AXPY> {
+  const void* y;
+  double b;
+  HopEpilogue(const DslashArgs& d) : y(d.y), b(d.b) {}
+  __device__ void expand(DslashArgs& d) const { d.y = y, d.a = 1.0, d.b = b; }
+};
+template <>
+struct HopEpilogue<EPI_AXPY_NORM> {
+  const void* y;
+  double b;
+  double *partial, *partial_pp[2];
+  HopEpilogue(const DslashArgs& d)
+      : y(d.y), b(d.b), partial(d.partial), partial_pp{d.partial_pp[0], d.partial_pp[1]} {}
+  __device__ void expand(DslashArgs& d) const {
+    d.y = y, d.a = 1.0, d.b = b, d.partial = partial, d.partial_pp[0] = partial_pp[0], d.partial_pp[1] = partial_pp[1];
+  }
+};
+template <>
+struct HopEpilogue<EPI_CG> {
+  const void* y;
+  double b;
+  double* partial_pp[2];
+  const double* alpha_in;
+  HopEpilogue(const DslashArgs& d)
+      : y(d.y), b(d.b), partial_pp{d.partial_pp[0], d.partial_pp[1]}, alpha_in(d.alpha_in) {}
+  __device__ void expand(DslashArgs& d) const {
+    d.y = y, d.a = 1.0, d.b = b, d.partial = nullptr, d.partial_pp[0] = partial_pp[0], d.partial_pp[1] = partial_pp[1];
+    d.r = d.out, d.alpha_in = alpha_in;
+  }
+};
+
+template <int EPI>
+struct HopOne {
+  int L[4];
+  unsigned mul[3];
+  unsigned packed;  // the three division shifts and the output parity, a byte each
+  const void *U, *in;
+  void* out;
+  const int* stop_at;
+  int base;   // the label base is this far behind *stop_at (0: none)
+  int label;  // without the base
+  HopEpilogue<EPI> x;
+
+  HopOne(const Lat& g, int out_par, const DslashArgs& d, int j)
+      : L{g.L[0], g.L[1], g.L[2], g.L[3]}, mul{g.mul[0], g.mul[1], g.mul[2]},
+        packed(g.shift[0] | g.shift[1] << 8 | g.shift[2] << 16 | (unsigned)out_par << 24), U(d.U), in(d.in), out(d.out),
+        stop_at(d.stop_at), base(d.label_base ? (int)(d.label_base - d.stop_at) : 0), label(d.iter0 + j), x(d) {}
+  // What the launch relies on.
+  static bool holds(const Lat& g, const DslashArgs& d) {
+    const long long V = (long long)g.L[0] * g.L[1] * g.L[2] * g.L[3];
+    return g.stride == g.Vh && 2LL * g.Vh == V && (!d.y || d.a == 1.0) && (!d.label_base || d.stop_at) &&
+           (EPI != EPI_CG || (d.r == d.out && !d.partial));
+  }
+};
+static_assert(sizeof(HopOne<EPI_PLAIN>) <= 112 && sizeof(HopOne<EPI_AXPY_NORM>) <= 112 && sizeof(HopOne<EPI_CG>) <= 112,
+              "launch arguments");
+struct HopBatch {  // blockIdx.y selects an entry of `table`
+  Lat g;
+  int out_par;
+  const DslashArgs* table;
+  int j;
+  HopBatch(const Lat& lat, int par, const DslashArgs* t, int jj) : g(lat), out_par(par), table(t), j(jj) {}
+};
+
 template <class SP, class LK, bool DAG, int EPI, bool BATCH>
-__global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par, const DslashArgs* __restrict__ table,
-                                                     DslashArgs one, int j) {
+__global__ void __launch_bounds__(kHopThreads) k_dslash_hops(std::conditional_t<BATCH, HopBatch, HopOne<EPI>> h) {
   using R = typename SP::R;
   constexpr int kSites = 64;
   __shared__ cx<R> half[8][6][kSites];
-  const DslashArgs* ep;
-  if constexpr (BATCH)
-    ep = table + blockIdx.y;
-  else
-    ep = &one;
+  Lat g;
+  DslashArgs one;
+  const DslashArgs* ep = &one;
+  int out_par, label;
+  if constexpr (BATCH) {
+    g = h.g;
+    ep = h.table + blockIdx.y;
+    out_par = h.out_par;
+    label = ep->iter0 + h.j;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g.L[k] = h.L[k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) g.mul[k] = h.mul[k], g.shift[k] = h.packed >> (8 * k) & 255;
+    g.Vh = g.stride = (h.L[0] >> 1) * h.L[1] * h.L[2] * h.L[3];
+    out_par = h.packed >> 24;
+    label = h.label;
+    one.U = h.U, one.in = h.in, one.out = h.out, one.stop_at = h.stop_at;
+    one.label_base = h.base ? h.stop_at + h.base : nullptr;
+    h.x.expand(one);
+  }
   const DslashArgs& e = *ep;
   // Everything the hop reads is requested before anything is waited for: the
   // solver control, the step length, block 0's partial sums, the epilogue's
@@ -409,8 +511,7 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
   // vain, so launches of which many are past it look at the control first: the
   // low-precision iterations queued up to the next reliable update, and the
   // gated launches of the update itself (which have no label base).
-  const int base = e.label_base ? *(const HMC_GLOBAL int*)e.label_base : 0;
-  const int label = e.iter0 + j + base;
+  if (e.label_base) label += *(const HMC_GLOBAL int*)e.label_base;
   int stop = INT_MAX;
   if (sizeof(R) == 4 || !e.label_base) {
     if (e.stop_at && label >= *(const HMC_GLOBAL int*)e.stop_at) return;
@@ -422,7 +523,7 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
   const bool sums = EPI == EPI_PLAIN && e.alpha_out && blockIdx.x == 0;
   double ta[kAlphaAhead], tb[kAlphaAhead];
   if (sums) {
-    const double* pp = e.alpha_pp[label & 1];
+    const double* pp = label & 1 ? e.alpha_pp[1] : e.alpha_pp[0];
 #pragma unroll
     for (int u = 0; u < kAlphaAhead; ++u) {
       const int i = threadIdx.x + u * kHopThreads;
@@ -430,7 +531,7 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
       tb[u] = i < e.alpha_n_den ? e.alpha_den[i] : 0.0;
     }
   }
-  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = xcd_remap(blockIdx.x, (g.Vh + kSites - 1) / kSites);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ls = threadIdx.x & (kSites - 1);
   const int s = b * kSites + ls;
@@ -520,7 +621,7 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(Lat g, int out_par,
     double v[2] = {0.0, 0.0};
 #pragma unroll
     for (int q = 0; q < kAlphaAhead; ++q) v[0] += ta[q], v[1] += tb[q];
-    const double* pp = e.alpha_pp[label & 1];
+    const double* pp = label & 1 ? e.alpha_pp[1] : e.alpha_pp[0];
     for (int i = threadIdx.x + kAlphaAhead * kHopThreads; i < e.alpha_n_pp; i += kHopThreads) v[0] += pp[i];
     for (int i = threadIdx.x + kAlphaAhead * kHopThreads; i < e.alpha_n_den; i += kHopThreads) v[1] += e.alpha_den[i];
     block_sum<2, 8>(v);
@@ -668,10 +769,21 @@ static hipError_t launch_typed(hmc_prec prec, int dagger, int epi, const LatArg&
   const size_t lds_cap = g.tiled && dslash_tiled_occupancy(ga, prec) == 2 ? 54000 : 0;
 #define HMC_LAUNCH(KERNEL) \
   hipExtLaunchKernelGGL(KERNEL, grid, block, lds_cap, st, ev.start, ev.stop, 0, g, out_par, table, one, j)
+#define HMC_HOPS(D, E, B)                                                                                         \
+  do {                                                                                                            \
+    if constexpr (B) {                                                                                            \
+      hipExtLaunchKernelGGL((k_dslash_hops<SP, LK, D, E, B>), grid, block, 0, st, ev.start, ev.stop, 0,           \
+                            HopBatch(g, out_par, table, j));                                                      \
+    } else {                                                                                                      \
+      if (!HopOne<E>::holds(g, one)) return hipErrorInvalidValue;                                                 \
+      hipExtLaunchKernelGGL((k_dslash_hops<SP, LK, D, E, B>), grid, block, 0, st, ev.start, ev.stop, 0,           \
+                            HopOne<E>(g, out_par, one, j));                                                       \
+    }                                                                                                             \
+  } while (0)
 #define HMC_DS_B(D, E, B)                                  \
   do {                                                     \
     if (shape == 4)                                        \
-      HMC_LAUNCH((k_dslash_hops<SP, LK, D, E, B>));        \
+      HMC_HOPS(D, E, B);                                   \
     else if (shape == 2)                                   \
       HMC_LAUNCH((k_dslash_split<SP, LK, D, E, B>));       \
     else                                                   \
@@ -700,6 +812,7 @@ static hipError_t launch_typed(hmc_prec prec, int dagger, int epi, const LatArg&
   }
 #undef HMC_DS
 #undef HMC_DS_B
+#undef HMC_HOPS
 #undef HMC_LAUNCH
   return hipGetLastError();
 }
