@@ -513,8 +513,7 @@ __device__ __forceinline__ void gauge_force_dir(const Lat& g, const void* U, dou
 // (48 KB).  The kernel is bound by its FP64 instructions (58% of the cycles
 // of 24^3x48) and the waits for the links that feed them, so each upper
 // plaquette of the block's sites is formed once for both of its links: two
-// rows a link, 24^3x48 271 -> 244 us, 48^3x96 4.83 -> 4.05 ms (there also the
-// change from ten reals a link).  Two of the directions take two of the six
+// rows a link, 24^3x48 271 -> 244 us, 48^3x96 4.56 -> 4.25 ms.  Two of the directions take two of the six
 // planes: which wavefronts (SIMDs) have them changes from block to block.
 // 24 KB and 128 registers, four blocks on a compute unit, lose 3%.
 template <class LK, bool NT>
