@@ -318,7 +318,7 @@ def run_hmc(args, H, torch):
     if rf:
         out["roofline"] = {"bound": "hbm", "achieved": rf["achieved"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": rf["achieved"] / HBM_PEAK_GBS, "traffic": load_traffic("hmc_16c32"),
-                           "kernel": ("F64 half-lattice hop, k_dslash or k_dslash_split (shape in "
+                           "kernel": ("F64 half-lattice hop, k_dslash, k_dslash_split or k_dslash_hops (shape in "
                                       "config.launch_shapes.dslash_f64; plain, axpy/norm and CG-update "
                                       "epilogues; link form in config.launch_shapes.dslash_links_f64)"),
                            "bytes": ("algorithmic: 1536 / 1728 / 1920 B per output site (8 links of 144 B, "
