@@ -1462,13 +1462,19 @@ hmc_status hmc_autotune(hmc_fields* f, const char* db_path, void* stream) {
       return us;
     };
     // shapes x link forms (linear order, no streaming), then streaming and
-    // the tiled orders x workgroups per CU for the best pair
+    // the tiled orders x workgroups per CU for the best pair.  Only the
+    // one-site shape has the orders, and they can make up for more than it
+    // trails by (48^3x96 FP64: 7.22 ms an iteration with a wavefront per hop,
+    // which leads in the linear order; one site in y-blocks 6.34), so its best
+    // form is tried in them also where another shape leads.
     int best = 0, best_form = 0, best_stream = 0, best_order = 0, best_occ = 2;
-    double best_us = 0;
+    int site_form = 0;
+    double best_us = 0, site_us = -1;
     for (int form : forms) {
       for (int shape : {1, 2, 4}) {
         const double us = time_candidate(shape, form, 0, 0, 2);
         if (us < 0) break;
+        if (shape == 1 && (site_us < 0 || us < site_us)) site_form = form, site_us = us;
         if (!best || us < best_us) best = shape, best_form = form, best_us = us;
       }
       if (status != HMC_OK) break;
@@ -1477,14 +1483,23 @@ hmc_status hmc_autotune(hmc_fields* f, const char* db_path, void* stream) {
       const double us = time_candidate(best, best_form, 1, 0, 2);
       if (us >= 0 && us < best_us) best_stream = 1, best_us = us;
     }
-    if (status == HMC_OK && best == 1 && tiled_order_valid(F->g)) {
+    if (status == HMC_OK && tiled_order_valid(F->g)) {
+      int site_stream = best_stream;
+      if (best != 1) {
+        site_stream = 0;
+        const double us = site_form ? time_candidate(1, site_form, 1, 0, 2) : -1;
+        if (us >= 0 && us < site_us) site_stream = 1;
+        if (us >= 0 && us < best_us) best = 1, best_form = site_form, best_stream = 1, best_us = us;
+      }
       // whole z-planes, then y-blocks of a few chunks
       for (int order : {1, 2, 3, 4, 6}) {
+        if (status != HMC_OK) break;
         if (!tiled_order_valid(F->g, order) || (order > 1 && order >= F->g.L[0] * F->g.L[1] / 128)) continue;
         for (int occ : {2, 0}) {
-          const double us = time_candidate(best, best_form, best_stream, order, occ);
+          const double us = time_candidate(1, site_form, site_stream, order, occ);
           if (us < 0) break;
-          if (us < best_us) best_order = order, best_occ = occ, best_us = us;
+          if (us < best_us)
+            best = 1, best_form = site_form, best_stream = site_stream, best_order = order, best_occ = occ, best_us = us;
         }
         if (status != HMC_OK) break;
       }
