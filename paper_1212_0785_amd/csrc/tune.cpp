@@ -190,15 +190,15 @@ int dslash_link_form(const LatArg& g, hmc_prec prec) {
   if (forced_link_form() > 0) return forced_link_form();
   const int t = tune_lookup(g.L, TUNE_DSLASH_LINKS, prec);
   if (t > 0) return t;
-  // The 10-real form saves a sixth of the link bytes and adds ~40 operations
-  // and a division per link: it pays once the links' bytes count, later for
-  // the 2-byte storages, whose hop is bound by its instructions sooner.
-  // Measured (Mhat, two rows / row 0 + column 2, us): FP64 12^3x24 13.4 /
-  // 13.7, 16^3x32 30.8 / 29.7, 20^3x40 71.5 / 69.8; FP32 12^3x24 11.1 / 12.1,
-  // 16^3x32 17.8 / 17.4, 24^3x48 75 / 68; FP16 24^3x48 46 / 51, 32^3x64
-  // 155 / 149; BF16 24^3x48 42 / 45, 32^3x64 149 / 138
-  const int from = prec == HMC_F64 || prec == HMC_F32 ? 1 << 16 : 1 << 20;
-  return g.Vh >= from ? LINK_ROWCOL : LINK_ROWS2;
+  // Two rows below 2^20 half-lattice sites: they rebuild a reunitarised FP64
+  // link bit for bit, row 0 and column 2 do not (error of Mhat at 24^3x44, two
+  // rows / row 0 + column 2: FP64 9.34e-17 / 9.92e-17, FP32 4.94e-8 / 5.08e-8,
+  // FP16 2.78e-4 / 2.80e-4).  From there a sixth fewer link bytes decide.
+  // Measured (Mhat, us, the same order): FP64 20^3x40 70.1 / 64.3, 24^3x44 140 /
+  // 128, 28^3x60 298 / 273; FP32 20^3x40 35.6 / 33.4, 28^3x60 171 / 159; FP16
+  // 24^3x48 51.8 / 45.9, 32^3x64 155 / 149; BF16 24^3x48 44.7 / 42.6, 32^3x64
+  // 149 / 138
+  return g.Vh >= 1 << 20 ? LINK_ROWCOL : LINK_ROWS2;
 }
 
 namespace {
