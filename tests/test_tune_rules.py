@@ -26,3 +26,8 @@ def test_links_keep_two_rows_below_2_20_sites(H):
         for L in (AT_2_16, BELOW_2_20):
             assert H.hmc_tune_query(L, H.TUNE_DSLASH_LINKS, prec) == (H.LINK_ROWS2, False), (L, prec)
         assert H.hmc_tune_query(FROM_2_20, H.TUNE_DSLASH_LINKS, prec) == (H.LINK_ROWCOL, False)
+
+
+@pytest.mark.parametrize("prec", [2, 3])
+def test_shipped_table_keeps_two_rows_for_the_halves_of_24c48(H, prec):
+    assert H.hmc_tune_query((24, 24, 24, 48), H.TUNE_DSLASH_LINKS, prec) == (H.LINK_ROWS2, True)
