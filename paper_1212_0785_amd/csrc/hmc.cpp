@@ -1472,6 +1472,7 @@ hmc_status hmc_autotune(hmc_fields* f, const char* db_path, void* stream) {
     double best_us = 0, site_us = -1;
     for (int form : forms) {
       for (int shape : {1, 2, 4}) {
+        if (dslash_run_shape(F->g.Vh, shape) != shape) continue;  // 1 would time 4 again
         const double us = time_candidate(shape, form, 0, 0, 2);
         if (us < 0) break;
         if (shape == 1 && (site_us < 0 || us < site_us)) site_form = form, site_us = us;

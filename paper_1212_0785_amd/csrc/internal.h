@@ -84,10 +84,10 @@ inline bool tiled_order_valid(const LatArg& g, int order = 1) {
 // The form a kernel reads: the compact one on SU(3) links, else all entries.
 inline int link_form_for(bool su3, int compact) { return su3 ? compact : (int)LINK_FULL; }
 inline int dslash_shape_blocks(int Vh, int shape) { return shape == 1 ? site_blocks(Vh) : ceil_div(Vh, kThreads / 4); }
-// The shape a launch runs: a lattice of fewer sites than one block of the
-// one-site shape has one wavefront per hop whatever the choice says (4^4,
-// Mhat: 8.8 us against 13.2 us, of which two launches take most).
-inline int dslash_run_shape(int Vh, int choice) { return Vh < kThreads ? 4 : choice; }
+// The shape a launch runs: choice 1 on a lattice that does not fill one of its
+// blocks has a wavefront per hop (FP64, us per CG iteration, 1 / 2 / 4: 4^3x8,
+// which just fills one, 41.0 / 29.1 / 20.3).
+inline int dslash_run_shape(int Vh, int choice) { return choice == 1 && Vh < kThreads ? 4 : choice; }
 inline int dslash_run_shape(const LatArg& g, hmc_prec prec) { return dslash_run_shape(g.Vh, dslash_shape(g, prec)); }
 inline int dslash_blocks(const LatArg& g, hmc_prec prec) {
   return dslash_shape_blocks(g.Vh, dslash_run_shape(g, prec));

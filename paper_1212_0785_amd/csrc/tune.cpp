@@ -279,7 +279,7 @@ int dslash_shape(const LatArg& g, hmc_prec prec) {
   // whose p-update adds four times the partial sums of the split shapes, us
   // per iteration: FP32 24^3x48 291 / 271 / 270, 32^3x64 844 / 894 / 887; FP16
   // 24^3x48 203 / 206 / 215; BF16 186 / 193 / 196)
-  // (below one block the choice has no effect: dslash_run_shape)
+  // (below one block choice 1 runs as 4: dslash_run_shape)
   if (prec == HMC_F64) return g.Vh < kThreads ? 1 : g.Vh < 3 << 19 ? 4 : 1;
   return g.Vh < (prec == HMC_F32 ? 1 << 19 : 1 << 18) ? 4 : 1;
 }
