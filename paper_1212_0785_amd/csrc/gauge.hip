@@ -702,7 +702,7 @@ static void gauge_force_typed(const LatArg& g, const void* U, double* P, double 
 hipError_t launch_gauge_force(const LatArg& g, const void* U, double* P, double coef_beta, hipStream_t st,
                               bool su3, int shape, int form) {
   if (shape < 0) shape = gauge_force_shape(g);
-  form = link_form_for(su3, form ? form : staple_run_form(g));
+  form = link_form_for(su3, form ? form : staple_link_form(g));
   const int lb = form == LINK_ROWCOL ? LkRowCol<LkF64>::kBytes : form == LINK_ROWS2 ? LkRows2<LkF64>::kBytes
                                                                                      : LkF64::kBytes;
   // per site: 4 links read, momenta read + written

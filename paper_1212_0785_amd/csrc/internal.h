@@ -57,7 +57,6 @@ int gauge_force_shape(const LatArg& g);
 // force follows FP64) and of the staple kernels (gauge force, plaquette).
 int dslash_link_form(const LatArg& g, hmc_prec prec);
 int staple_link_form(const LatArg& g);
-int staple_run_form(const LatArg& g);  // what a launch reads
 // Whether the Dslash at storage prec streams: non-temporal loads of its
 // (compact) links and stores of its output, which keep that once-used data
 // from displacing the neighbour spinors in L2 (pays at large volumes) but
@@ -297,7 +296,7 @@ int plaquette_blocks(const LatArg& g, bool su3);
 hipError_t launch_plaquette_partials(const LatArg& g, const void* U, double* part, hipStream_t st, bool su3);
 hipError_t launch_kinetic_partials(const LatArg& g, const double* P, double* part, int nb, hipStream_t st);
 // shape: -1 = gauge_force_shape(), 0 / 1 / 2 = fixed; form: 0 =
-// staple_run_form(), else a fixed compact form (used on SU(3) links only).
+// staple_link_form(), else a fixed compact form (used on SU(3) links only).
 hipError_t launch_gauge_force(const LatArg& g, const void* U, double* P, double coef_beta, hipStream_t st,
                               bool su3, int shape = -1, int form = 0);
 // su3: U is SU(3) to rounding (rows 0 and 1 read, row 2 rebuilt).

@@ -245,20 +245,18 @@ int dslash_tiled_occupancy(const LatArg& g, hmc_prec prec) {
   return 2;
 }
 
-static int staple_form(const LatArg& g, int rule) {
+int staple_link_form(const LatArg& g) {
   if (forced_link_form() > 0) return forced_link_form();
   const int t = tune_lookup(g.L, TUNE_GFORCE_LINKS, HMC_F64);
-  return t > 0 ? t : rule;
+  if (t > 0) return t;
+  // measured on MI355X, ten reals a link against twelve: 8^4 10.4 and 8.3 us,
+  // 18x10x14x26 34.1 and 27.4, 20^3x40 141 and 112, 32^3x64 893 and 782, 48^3x96
+  // 4.64 and 3.98 ms (the kernel waits for its arithmetic before its bytes).
+  // Below 256 half-lattice sites the launch follows the answer that callers
+  // have had from the query there, ten, though twelve are faster (4^3x6 10.2
+  // and 8.1 us).
+  return g.Vh < kThreads ? LINK_ROWCOL : LINK_ROWS2;
 }
-
-// measured on MI355X, ten reals a link against twelve: 4^3x6 12.7 and 9.7 us,
-// 18x10x14x26 33.5 and 27.3, 20^3x40 145 and 117, 32^3x64 965 and 809, 48^3x96
-// 4.83 and 4.05 ms (the kernel waits for its arithmetic before its bytes).
-// Below one block of 256 sites the choice reported without an entry is still
-// ten reals, as for the Dslash shape it is one site per work-item; the launch
-// reads two rows at every size.
-int staple_link_form(const LatArg& g) { return staple_form(g, g.Vh < kThreads ? LINK_ROWCOL : LINK_ROWS2); }
-int staple_run_form(const LatArg& g) { return staple_form(g, LINK_ROWS2); }
 
 int dslash_shape(const LatArg& g, hmc_prec prec) {
   static const int forced = [] {
@@ -323,7 +321,7 @@ int plaquette_link_form(const LatArg& g) {
   // with row 0 + column 2 at 48^3x96, 21.4 against 29.6 us at 16^3x32 (the
   // reconstruction lengthens the latency-bound chain); the per-site form
   // follows the staple force
-  return plaquette_shape(g) == 1 ? (int)LINK_ROWS2 : staple_run_form(g);
+  return plaquette_shape(g) == 1 ? (int)LINK_ROWS2 : staple_link_form(g);
 }
 
 

@@ -43,3 +43,23 @@ def test_shape_entries_reach_the_launch_below_one_block(H, tmp_path):
         got[shape] = get_spinor(H, F, out, 0, prec=H.F16)
     assert np.array_equal(got[1], got[4])
     assert not np.array_equal(got[2], got[4])
+
+
+@pytest.mark.parametrize("L", [(2, 6, 4, 4), (2, 6, 8, 8)])
+def test_staple_force_reads_the_reported_form(H, L):
+    """96 and 384 half-lattice sites: the bytes of the launch are those of the
+    form that the query reports."""
+    F = H.Fields(L, 5.6, 0.13)
+    put_gauge(H, F, synth.gauge_field(93, L, eps=0.4))
+    assert H.hmc_links_two_row(F)
+    H.hmc_timing_reset()
+    H.hmc_timing_enable(1)
+    H.hmc_gauge_force(F, 0.1)
+    torch.cuda.synchronize()
+    t = H.hmc_timing_read()["gauge_force"]
+    H.hmc_timing_enable(0)
+    H.hmc_timing_reset()
+    form, tuned = H.hmc_tune_query(L, H.TUNE_GAUGE_FORCE_LINKS)
+    assert not tuned and t["launches"] == 1
+    # per site four links of `form` reals, eight momenta a link read and written
+    assert t["bytes_moved"] == np.prod(L) * 4 * (8 * form + 2 * 64)
