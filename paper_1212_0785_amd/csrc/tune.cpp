@@ -230,11 +230,13 @@ int dslash_tiled_order(const LatArg& g, hmc_prec prec) {
   if (forced >= 0) return forced == 0 ? 0 : tiled_order_valid(g, forced) ? forced : 1;
   const int t = tune_lookup(g.L, TUNE_DSLASH_ORDER, prec);
   if (t >= 0) return t == 0 ? 0 : tiled_order_valid(g, t) ? t : 1;
-  // whole z-planes for FP64 once a t-slice outgrows an XCD's L2 (linear /
-  // tiled with two blocks per CU, Mhat: 32^3x64 507 / 493 us, 40^3x80 1349 /
-  // 1274 us); the narrower storages gain nothing from it (40^3x80 FP32 698 /
-  // 739, BF16 324 / 548 us)
-  return prec == HMC_F64 && g.Vh >= (1 << 20) ? 1 : 0;
+  // Whole z-planes for FP64 where its rule has one site per work-item, once a
+  // t-slice outgrows an XCD's L2 (linear / tiled with two blocks per CU, Mhat:
+  // 32^3x64 495 / 502 us, 40^3x80 1333 / 1255).  The narrower storages stay
+  // linear: the cap costs them (40^3x80, linear / tiled with / without it: FP32
+  // 680 / 682 / 666 us, FP16 341 / 434 / 336, BF16 323 / 424 / 320), and what
+  // is left without it is nothing at 32^3x64 (258 / 259, 150 / 151, 146 / 142).
+  return prec == HMC_F64 && g.Vh >= 3 << 19 && dslash_shape(g, prec) == 1 ? 1 : 0;
 }
 
 int dslash_tiled_occupancy(const LatArg& g, hmc_prec prec) {
