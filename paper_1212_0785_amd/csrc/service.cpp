@@ -91,10 +91,7 @@ size_t carve_request(char* base, const LatArg& g, int prec, SolveVecs* v, void**
   s.pp[0] = (double*)c.take(np * 8);
   s.pp[1] = (double*)c.take(np * 8);
   s.pq = (double*)c.take(np * 8);
-  (void)c.take((size_t)nbR * 8);
-  // the update's partials (at most one per 64 sites) use the odd half of the
-  // solution, which is written when the solve ends
-  s.pr = *x ? (double*)((char*)*x + h64) : nullptr;
+  s.pr = (double*)c.take((size_t)cg_vec_blocks(Vh) * 8);
   s.red = (double*)c.take((size_t)2 * nbR * 8);
   s.nbD = nbD;
   s.nbR = nbR;
