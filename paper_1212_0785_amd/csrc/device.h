@@ -722,8 +722,32 @@ struct SpBF16 {
   }
 };
 
+// Whole-link load where mu and par are uniform over the wavefront, in two steps
+// like that of the compact forms: the stored reals, and what is rebuilt from
+// them (nothing here).
+template <class LK, typename Real>
+struct WholeLink {
+  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<Real>& u) {
+    u.m[0] = LK::template one_u<0>(base, stride, mu, par, s);
+    u.m[1] = LK::template one_u<1>(base, stride, mu, par, s);
+    u.m[2] = LK::template one_u<2>(base, stride, mu, par, s);
+    u.m[3] = LK::template one_u<3>(base, stride, mu, par, s);
+    u.m[4] = LK::template one_u<4>(base, stride, mu, par, s);
+    u.m[5] = LK::template one_u<5>(base, stride, mu, par, s);
+    u.m[6] = LK::template one_u<6>(base, stride, mu, par, s);
+    u.m[7] = LK::template one_u<7>(base, stride, mu, par, s);
+    u.m[8] = LK::template one_u<8>(base, stride, mu, par, s);
+  }
+  __device__ static void finish_u(const void*, int, int, int, int, mat3<Real>&) {}
+  __device__ static mat3<Real> load_u(const void* base, int stride, int mu, int par, int s) {
+    mat3<Real> u;
+    raw_u(base, stride, mu, par, s, u);
+    return u;
+  }
+};
+
 // Links: element (mu, parity, k, s) at ((mu*2 + parity)*9 + k)*stride + s.
-struct LkF64 {
+struct LkF64 : WholeLink<LkF64, double> {
   static constexpr bool kStream = false;
   using R = double;
   static constexpr int kBytes = 144;
@@ -754,25 +778,6 @@ struct LkF64 {
     v2d t = gld_link<v2d, NT>(comp<v2d>(base, (mu * 2 + par) * 9 + K, stride), s);
     return {t.x, t.y};
   }
-  // load (mu, par uniform) in two steps: the stored reals, and what is rebuilt
-  // from them (nothing here)
-  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
-    u.m[0] = one_u<0>(base, stride, mu, par, s);
-    u.m[1] = one_u<1>(base, stride, mu, par, s);
-    u.m[2] = one_u<2>(base, stride, mu, par, s);
-    u.m[3] = one_u<3>(base, stride, mu, par, s);
-    u.m[4] = one_u<4>(base, stride, mu, par, s);
-    u.m[5] = one_u<5>(base, stride, mu, par, s);
-    u.m[6] = one_u<6>(base, stride, mu, par, s);
-    u.m[7] = one_u<7>(base, stride, mu, par, s);
-    u.m[8] = one_u<8>(base, stride, mu, par, s);
-  }
-  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>&) {}
-  __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
-    mat3<R> u;
-    raw_u(base, stride, mu, par, s, u);
-    return u;
-  }
   __device__ static void store(void* base, int stride, int mu, int par, int s, const mat3<R>& u) {
     void* p = (char*)base + (size_t)(mu * 2 + par) * 9 * stride * sizeof(v2d);
 #pragma unroll
@@ -780,7 +785,7 @@ struct LkF64 {
   }
 };
 
-struct LkF32 {
+struct LkF32 : WholeLink<LkF32, float> {
   static constexpr bool kStream = false;
   using R = float;
   static constexpr int kBytes = 72;
@@ -808,25 +813,6 @@ struct LkF32 {
     v2f t = gld_link<v2f, NT>(comp<v2f>(base, (mu * 2 + par) * 9 + K, stride), s);
     return {t.x, t.y};
   }
-  // load (mu, par uniform) in two steps: the stored reals, and what is rebuilt
-  // from them (nothing here)
-  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
-    u.m[0] = one_u<0>(base, stride, mu, par, s);
-    u.m[1] = one_u<1>(base, stride, mu, par, s);
-    u.m[2] = one_u<2>(base, stride, mu, par, s);
-    u.m[3] = one_u<3>(base, stride, mu, par, s);
-    u.m[4] = one_u<4>(base, stride, mu, par, s);
-    u.m[5] = one_u<5>(base, stride, mu, par, s);
-    u.m[6] = one_u<6>(base, stride, mu, par, s);
-    u.m[7] = one_u<7>(base, stride, mu, par, s);
-    u.m[8] = one_u<8>(base, stride, mu, par, s);
-  }
-  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>&) {}
-  __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
-    mat3<R> u;
-    raw_u(base, stride, mu, par, s, u);
-    return u;
-  }
   __device__ static void store(void* base, int stride, int mu, int par, int s, const mat3<double>& u) {
     void* p = (char*)base + (size_t)(mu * 2 + par) * 9 * stride * sizeof(v2f);
 #pragma unroll
@@ -834,7 +820,7 @@ struct LkF32 {
   }
 };
 
-struct LkF16 {
+struct LkF16 : WholeLink<LkF16, float> {
   static constexpr bool kStream = false;
   using R = float;
   static constexpr int kBytes = 36;
@@ -862,25 +848,6 @@ struct LkF16 {
     v2f t = __builtin_convertvector(gld_link<v2h, NT>(comp<v2h>(base, (mu * 2 + par) * 9 + K, stride), s), v2f);
     return {t.x, t.y};
   }
-  // load (mu, par uniform) in two steps: the stored reals, and what is rebuilt
-  // from them (nothing here)
-  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
-    u.m[0] = one_u<0>(base, stride, mu, par, s);
-    u.m[1] = one_u<1>(base, stride, mu, par, s);
-    u.m[2] = one_u<2>(base, stride, mu, par, s);
-    u.m[3] = one_u<3>(base, stride, mu, par, s);
-    u.m[4] = one_u<4>(base, stride, mu, par, s);
-    u.m[5] = one_u<5>(base, stride, mu, par, s);
-    u.m[6] = one_u<6>(base, stride, mu, par, s);
-    u.m[7] = one_u<7>(base, stride, mu, par, s);
-    u.m[8] = one_u<8>(base, stride, mu, par, s);
-  }
-  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>&) {}
-  __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
-    mat3<R> u;
-    raw_u(base, stride, mu, par, s, u);
-    return u;
-  }
   __device__ static void store(void* base, int stride, int mu, int par, int s, const mat3<double>& u) {
     void* p = (char*)base + (size_t)(mu * 2 + par) * 9 * stride * sizeof(v2h);
 #pragma unroll
@@ -889,7 +856,7 @@ struct LkF16 {
   }
 };
 
-struct LkBF16 {
+struct LkBF16 : WholeLink<LkBF16, float> {
   static constexpr bool kStream = false;
   using R = float;
   static constexpr int kBytes = 36;
@@ -916,25 +883,6 @@ struct LkBF16 {
   __device__ static cx<R> one_u(const void* base, int stride, int mu, int par, int s) {
     uint32_t w = gld_link<uint32_t, NT>(comp<uint32_t>(base, (mu * 2 + par) * 9 + K, stride), s);
     return {bf16_to_f(w & 0xffffu), bf16_to_f(w >> 16)};
-  }
-  // load (mu, par uniform) in two steps: the stored reals, and what is rebuilt
-  // from them (nothing here)
-  __device__ static void raw_u(const void* base, int stride, int mu, int par, int s, mat3<R>& u) {
-    u.m[0] = one_u<0>(base, stride, mu, par, s);
-    u.m[1] = one_u<1>(base, stride, mu, par, s);
-    u.m[2] = one_u<2>(base, stride, mu, par, s);
-    u.m[3] = one_u<3>(base, stride, mu, par, s);
-    u.m[4] = one_u<4>(base, stride, mu, par, s);
-    u.m[5] = one_u<5>(base, stride, mu, par, s);
-    u.m[6] = one_u<6>(base, stride, mu, par, s);
-    u.m[7] = one_u<7>(base, stride, mu, par, s);
-    u.m[8] = one_u<8>(base, stride, mu, par, s);
-  }
-  __device__ static void finish_u(const void*, int, int, int, int, mat3<R>&) {}
-  __device__ static mat3<R> load_u(const void* base, int stride, int mu, int par, int s) {
-    mat3<R> u;
-    raw_u(base, stride, mu, par, s, u);
-    return u;
   }
   __device__ static void store(void* base, int stride, int mu, int par, int s, const mat3<double>& u) {
     void* p = (char*)base + (size_t)(mu * 2 + par) * 9 * stride * sizeof(uint32_t);
