@@ -404,10 +404,11 @@ hmc_status hmc_stream_triad(void* a, const void* b, const void* c, double s, uin
  *   HMC_TUNE_DSLASH (per storage precision): 1 = one site per work-item, in
  *     blocks of 256 (on a lattice of fewer than 256 half-lattice sites, which
  *     does not fill one such block, 1 runs as 4 does), 2 = two wavefronts per
- *     64-site group, two directions each, 4 = eight, one hop each.  The hops
- *     of Mhat outside a solve on at most 128 half-lattice sites (hmc_mhat,
- *     the refresh, the chronological guess) run in one launch of their own,
- *     of which only the link form is chosen here;
+ *     64-site group, two directions each, 4 = eight, one hop each (in the
+ *     batches of the solve service from 2^15 half-lattice sites on: four, one
+ *     direction each).  The hops of Mhat outside a solve on at most 128
+ *     half-lattice sites (hmc_mhat, the refresh, the chronological guess) run
+ *     in one launch of their own, of which only the link form is chosen here;
  *   HMC_TUNE_GAUGE_FORCE (prec HMC_F64): 0 = one link per work-item,
  *     direction by direction; 1 = plane split; 2 = a block per 64 sites and
  *     all four directions, in the tiled walk of the Dslash where the lattice

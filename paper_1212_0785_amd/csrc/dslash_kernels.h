@@ -183,18 +183,18 @@ __global__ void __launch_bounds__(kBlock) HMC_DSLASH_WAVES k_dslash(Lat g, int o
   }
 }
 
-// Two-way direction split: a block of two wavefronts covers 64 sites;
-// wavefront w computes the hops along directions 2w and 2w + 1 and parks its
-// partial sum in LDS; after a barrier each work-item combines the two
-// partials of six of the 12 components of one site (coalesced stores).
-// Twice the wavefronts of the one-site-per-work-item kernel at the same
-// registers per work-item, and half of its serial hop chain.
-template <class SP, class LK, bool DAG, int EPI, bool BATCH>
-__global__ void __launch_bounds__(128) k_dslash_split(Lat g, int out_par, const DslashArgs* __restrict__ table,
+// Direction split: a block of NW = 2 or 4 wavefronts covers 64 sites; wavefront
+// w computes the hops along two directions, 2w and 2w + 1, or along direction w,
+// and parks its partial sum in LDS; after a barrier each work-item combines the
+// partials of 12 / NW of the 12 components of one site (coalesced stores).  NW
+// times the wavefronts of the one-site-per-work-item kernel at the same registers
+// per work-item, and 1 / NW of its serial hop chain.
+template <class SP, class LK, bool DAG, int EPI, bool BATCH, int NW>
+__global__ void __launch_bounds__(64 * NW) k_dslash_split(Lat g, int out_par, const DslashArgs* __restrict__ table,
                                                       DslashArgs one, int j) {
   using R = typename SP::R;
-  constexpr int kSites = 64;
-  __shared__ cx<R> part[2][12][kSites];
+  constexpr int kSites = 64, NC = 12 / NW;
+  __shared__ cx<R> part[NW][12][kSites];
   const DslashArgs* ep;
   if constexpr (BATCH)
     ep = table + blockIdx.y;
@@ -203,7 +203,7 @@ __global__ void __launch_bounds__(128) k_dslash_split(Lat g, int out_par, const 
   const DslashArgs& e = *ep;
   const int label = e.iter0 + j + (e.label_base ? *(const HMC_GLOBAL int*)e.label_base : 0);
   if (e.stop_at && label >= *(const HMC_GLOBAL int*)e.stop_at) return;
-  alpha_prologue<2>(e, label);
+  alpha_prologue<NW>(e, label);
   const int b = xcd_remap(blockIdx.x, gridDim.x);
   const int w = threadIdx.x >> 6;  // wave index (uniform per wave)
   const int ls = threadIdx.x & (kSites - 1);
@@ -214,7 +214,14 @@ __global__ void __launch_bounds__(128) k_dslash_split(Lat g, int out_par, const 
     for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
     if (s < g.Vh) {
       const Site st = cb_site(g, out_par, s);
-      if (w == 0) {
+      if constexpr (NW == 4) {
+        switch (w) {
+          case 0: hop_dir<SP, LK, 0, DAG>(g, st, out_par, s, e.U, e.in, acc); break;
+          case 1: hop_dir<SP, LK, 1, DAG>(g, st, out_par, s, e.U, e.in, acc); break;
+          case 2: hop_dir<SP, LK, 2, DAG>(g, st, out_par, s, e.U, e.in, acc); break;
+          default: hop_dir<SP, LK, 3, DAG>(g, st, out_par, s, e.U, e.in, acc); break;
+        }
+      } else if (w == 0) {
         hop_dir<SP, LK, 0, DAG>(g, st, out_par, s, e.U, e.in, acc);
         hop_dir<SP, LK, 1, DAG>(g, st, out_par, s, e.U, e.in, acc);
       } else {
@@ -226,19 +233,23 @@ __global__ void __launch_bounds__(128) k_dslash_split(Lat g, int out_par, const 
     for (int k = 0; k < 12; ++k) part[w][k][ls] = acc[k];
   }
   __syncthreads();
-  // work-item (ls, w) now owns components 6 w .. 6 w + 5 of site s
+  // work-item (ls, w) now owns components NC w .. NC w + NC - 1 of site s
   double nrm[1] = {0.0};
-  cx<R> o[6];
+  cx<R> o[NC];
   const bool active = s < g.Vh;
   if (active) {
 #pragma unroll
-    for (int c = 0; c < 6; ++c) o[c] = part[0][6 * w + c][ls] + part[1][6 * w + c][ls];
+    for (int c = 0; c < NC; ++c) {
+      o[c] = part[0][NC * w + c][ls];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) o[c] = o[c] + part[q][NC * w + c][ls];
+    }
     if (EPI != EPI_PLAIN) {
       const R a = (R)e.a, bb = (R)e.b;
 #pragma unroll
-      for (int c = 0; c < 6; ++c) {
+      for (int c = 0; c < NC; ++c) {
         if (e.y) {
-          const cx<R> y = SP::load_one(e.y, g.stride, s, 6 * w + c);
+          const cx<R> y = SP::load_one(e.y, g.stride, s, NC * w + c);
           o[c] = {fma(bb, o[c].re, a * y.re), fma(bb, o[c].im, a * y.im)};
         } else {
           o[c] = bb * o[c];
@@ -248,38 +259,41 @@ __global__ void __launch_bounds__(128) k_dslash_split(Lat g, int out_par, const 
     if (EPI == EPI_CG) {
       const R al = (R)(*(const HMC_GLOBAL double*)e.alpha_in);
 #pragma unroll
-      for (int c = 0; c < 6; ++c) {
-        const cx<R> rv = SP::load_one(e.r, g.stride, s, 6 * w + c);
+      for (int c = 0; c < NC; ++c) {
+        const cx<R> rv = SP::load_one(e.r, g.stride, s, NC * w + c);
         o[c] = {fma(-al, o[c].re, rv.re), fma(-al, o[c].im, rv.im)};
       }
     }
     if (EPI == EPI_AXPY_NORM || EPI == EPI_CG)
 #pragma unroll
-      for (int c = 0; c < 6; ++c) nrm[0] += (double)o[c].re * o[c].re + (double)o[c].im * o[c].im;
+      for (int c = 0; c < NC; ++c) nrm[0] += (double)o[c].re * o[c].re + (double)o[c].im * o[c].im;
   }
   if constexpr (SP::kScaled) {
     // the per-site scale needs the largest |re|, |im| over all 12 components
-    __shared__ float smax[2][kSites];
+    __shared__ float smax[NW][kSites];
     float m = 0.f;
     if (active)
 #pragma unroll
-      for (int c = 0; c < 6; ++c) m = fmaxf(m, fmaxf(fabsf((float)o[c].re), fabsf((float)o[c].im)));
+      for (int c = 0; c < NC; ++c) m = fmaxf(m, fmaxf(fabsf((float)o[c].re), fabsf((float)o[c].im)));
     smax[w][ls] = m;
     __syncthreads();
-    m = SP::live_scale(fmaxf(smax[0][ls], smax[1][ls]));
+    m = smax[0][ls];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) m = fmaxf(m, smax[q][ls]);
+    m = SP::live_scale(m);
     const float inv = m > 0.f ? 1.f / m : 0.f;
     if (active) {
       if (w == 0) SP::template store_scale<LK::kStream>(e.out, g.stride, s, m);
 #pragma unroll
-      for (int c = 0; c < 6; ++c) SP::template store_one_scaled<LK::kStream>(e.out, g.stride, s, 6 * w + c, o[c], inv);
+      for (int c = 0; c < NC; ++c) SP::template store_one_scaled<LK::kStream>(e.out, g.stride, s, NC * w + c, o[c], inv);
     }
   } else {
     if (active)
 #pragma unroll
-      for (int c = 0; c < 6; ++c) SP::template store_one<LK::kStream>(e.out, g.stride, s, 6 * w + c, o[c]);
+      for (int c = 0; c < NC; ++c) SP::template store_one<LK::kStream>(e.out, g.stride, s, NC * w + c, o[c]);
   }
   if (EPI == EPI_AXPY_NORM || EPI == EPI_CG) {
-    block_sum<1, 2>(nrm);
+    block_sum<1, NW>(nrm);
     put_partial(e, label, b, nrm[0]);
   }
 }
@@ -742,6 +756,14 @@ hipError_t launch_mhat_small_links(hmc_prec prec, int dagger, const LatArg& g, c
   return hipGetLastError();
 }
 
+// Batched launches of the hop-per-wavefront shape split by direction instead from
+// kBatchSites on: what they wait for there is their bytes, which four wavefronts
+// of two hops each request with half the LDS traffic and barriers a wavefront.
+// Requests in the service, hop / direction per wavefront, ms: FP32 12^3x24 one
+// 2.78 / 2.80, four 5.66 / 5.43; 14^3x28 3.36 / 3.40, 8.27 / 7.85; 16^3x32 3.99 /
+// 3.96, 11.8 / 11.1, sixteen 57.8 / 51.9; 24^3x48 14.7 / 13.8, 63.3 / 56.6; FP64
+// 12^3x24 2.41 / 2.57, 6.47 / 6.15; 14^3x28 3.56 / 3.39, 10.6 / 9.9; 16^3x32
+// sixteen 89.0 / 76.6.
 template <class SP, class LK>
 static hipError_t launch_typed(hmc_prec prec, int dagger, int epi, const LatArg& ga, int out_par,
                                const DslashArgs* table, int nbatch, const DslashArgs& one, hipStream_t st, int j,
@@ -758,7 +780,8 @@ static hipError_t launch_typed(hmc_prec prec, int dagger, int epi, const LatArg&
     g.tile_y = order == 1 ? g.tile_r : order;  // 0: chunks of the t-slices
   }
   const dim3 grid(dslash_shape_blocks(ga.Vh, shape), nbatch);
-  const dim3 block(shape == 4 ? kHopThreads : shape == 2 ? 128 : kBlock);
+  const bool four = table && shape == 4 && ga.Vh >= kBatchSites;
+  const dim3 block(four ? 256 : shape == 4 ? kHopThreads : shape == 2 ? 128 : kBlock);
   // The tiled order may reserve LDS it does not use: 54,000 bytes per block
   // leave room for two blocks per CU (2 wavefronts per SIMD), so an XCD's
   // wavefronts in flight span a few (z, t) rows instead of dozens and the
@@ -780,14 +803,16 @@ static hipError_t launch_typed(hmc_prec prec, int dagger, int epi, const LatArg&
                             HopOne<E>(g, out_par, one, j));                                                       \
     }                                                                                                             \
   } while (0)
-#define HMC_DS_B(D, E, B)                                  \
-  do {                                                     \
-    if (shape == 4)                                        \
-      HMC_HOPS(D, E, B);                                   \
-    else if (shape == 2)                                   \
-      HMC_LAUNCH((k_dslash_split<SP, LK, D, E, B>));       \
-    else                                                   \
-      HMC_LAUNCH((k_dslash<SP, LK, D, E, B>));             \
+#define HMC_DS_B(D, E, B)                                       \
+  do {                                                          \
+    if (B && four) /* (four wavefronts: in batches only) */     \
+      HMC_LAUNCH((k_dslash_split<SP, LK, D, E, B, B ? 4 : 2>)); \
+    else if (shape == 4)                                        \
+      HMC_HOPS(D, E, B);                                        \
+    else if (shape == 2)                                        \
+      HMC_LAUNCH((k_dslash_split<SP, LK, D, E, B, 2>));         \
+    else                                                        \
+      HMC_LAUNCH((k_dslash<SP, LK, D, E, B>));                  \
   } while (0)
 #define HMC_DS(D, E)            \
   do {                          \

@@ -91,6 +91,11 @@ inline int dslash_run_shape(const LatArg& g, hmc_prec prec) { return dslash_run_
 inline int dslash_blocks(const LatArg& g, hmc_prec prec) {
   return dslash_shape_blocks(g.Vh, dslash_run_shape(g, prec));
 }
+// Half-lattice sites from which a batched launch is bound by its bytes even for
+// one request and takes the forms that move them fastest rather than those that
+// answer soonest.  By volume alone, so that a request's result does not depend on
+// what it is batched with.
+constexpr int kBatchSites = 1 << 15;
 // Largest block count (and Dslash-epilogue partial count) of any shape.
 inline int dslash_blocks_max(int Vh) { return ceil_div(Vh, kThreads / 4); }
 // Tuning table: -1 when absent; load/save return entries read/written or -1.

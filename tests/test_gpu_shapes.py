@@ -107,19 +107,22 @@ def test_shapes_on_ragged_lattices(H, tmp_path, L, shape, su3):
         assert rel(get_spinor(H, F, x, 0), want) < 1e-12
 
 
+# 320 half-lattice sites, and 35672 (ragged too), where the batches of shape 4
+# split by direction
 @pytest.mark.parametrize("prec", range(4))
-@pytest.mark.parametrize("shape", [1, 2, 4])
-def test_batched_shapes_on_a_ragged_lattice(H, tmp_path, shape, prec):
+@pytest.mark.parametrize("L,shape", [(RAGGED_L[0], 1), (RAGGED_L[0], 2), (RAGGED_L[0], 4), ((14, 14, 14, 26), 4)])
+def test_batched_shapes_on_a_ragged_lattice(H, tmp_path, L, shape, prec):
     """Two requests of one volume in one batch: each is what it is alone, bit
     for bit, and solves its system (the oracle's solution to 1e-8: both meet
     |b - M x| <= 1e-10 |b|)."""
-    L = RAGGED_L[0]
-    load(H, tmp_path, [f"dslash 4 8 2 10 {p} {shape} 0" for p in range(4)])
+    ext = " ".join(map(str, L))
+    load(H, tmp_path, [f"dslash {ext} {p} {shape} 0" for p in range(4)])
     reqs = [(L, 0.150, 97, 0.3, 1, 3), (L, 0.154, 98, 0.4, 0, 5)]
-    res, outs = run_manual(H, reqs, prec)
+    arena = 2 * H.hmc_request_bytes(H.solve_request(*reqs[0]), prec) + (4 << 20)  # two requests and the header
+    res, outs = run_manual(H, reqs, prec, arena=arena)
     assert all(r["status"] == 0 and r["true_rel_res"] <= 1e-10 and r["max_group"] == 2 for r in res)
     for (lat, k, gs, eps, kind, ss), out in zip(reqs, outs):
-        _, alone = run_manual(H, [(lat, k, gs, eps, kind, ss)], prec)
+        _, alone = run_manual(H, [(lat, k, gs, eps, kind, ss)], prec, arena=arena)
         assert torch.equal(alone[0], out)
         want, _ = O.wilson_solve(lat, O.weak_field(lat, gs, eps), k, O.source(lat, kind, ss, 0), tol=1e-12)
         assert rel(to_canon(H, lat, out), want) < 1e-8
