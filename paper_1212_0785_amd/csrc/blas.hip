@@ -276,52 +276,65 @@ __device__ __forceinline__ const CgArgs& cg_args(const CgBatch& h, int* label, i
 // to the p-update in both, which reads p anyway: with x in the CGLS update p
 // was read twice (24^3x48, FP64: update 67 -> 34 us, p-update 39 -> 54).
 //
-// Four work-items share a site in both kernels: work-item (part, s) updates the
+// NP = 4 work-items share a site in both kernels: work-item (part, s) updates the
 // components 3 part .. 3 part + 2 of site s.  For a storage with a per-site
 // scale, which needs all twelve components, the four are the wavefronts of one
-// block, which exchange their largest components through LDS.  XCD x (hardware blocks b with b % 8 == x;
-// their number is a multiple of 8) takes the sites [x Vh / 8, (x + 1) Vh / 8),
-// the range the Dslash's XCD-aware block order gives the same XCD, so the
-// vectors stay in the L2 of the XCD that reads them next.  The first element's
-// loads depend on no sum and are issued before anything is waited for.
+// block, which exchange their largest components through LDS.  Batches from
+// kBatchSites on have work-items enough with one per site (NP = 1), and a quarter
+// of the blocks then repeats the sums over the partials (requests in the service,
+// four parts / one, ms: sixteen of 16^3x32 FP64 75.5 / 76.0, FP32 52.1 / 50.0,
+// FP16 46.6 / 43.6, BF16 45.4 / 42.4; one FP32 3.95 / 3.93; but one of 8^3x16 FP64
+// 1.70 / 1.79).  XCD x (hardware blocks b with b % 8 == x; their number is a
+// multiple of 8) takes the sites [x Vh / 8, (x + 1) Vh / 8), the range the
+// Dslash's XCD-aware block order gives the same XCD, so the vectors stay in the
+// L2 of the XCD that reads them next.  The first element's loads depend on no sum
+// and are issued before anything is waited for, but where many launches are past
+// their stop.
 struct VecRange {
   int lo, nsx, nwork, first, step;
 };
-// Element i of a range is part i / nsx of site lo + i % nsx; SCALED: wavefront
-// w of a block has part w of 64 sites, so i runs over groups of 64 sites times
-// four parts, and all four wavefronts of a block make the same steps.
-template <bool SCALED>
+// Element i of a range is part i / nsx of site lo + i % nsx (NP = 1: site
+// lo + i); SHARED: wavefront w of a block has part w of 64 sites, so i runs over
+// groups of 64 sites times four parts, and all four wavefronts of a block make
+// the same steps.
+template <int NP, bool SHARED>
 __device__ __forceinline__ VecRange vec_range(int Vh, int nbx) {
   VecRange v;
   const int xcd = blockIdx.x & 7;
   v.lo = (int)((long long)Vh * xcd / 8);
   v.nsx = (int)((long long)Vh * (xcd + 1) / 8) - v.lo;
-  v.nwork = SCALED ? (v.nsx + 63) / 64 * kBlock : v.nsx * 4;
+  v.nwork = SHARED ? (v.nsx + 63) / 64 * kBlock : v.nsx * NP;
   v.first = (blockIdx.x >> 3) * kBlock + threadIdx.x;
   v.step = nbx * kBlock;
   return v;
 }
 // Part and site of element i (site -1: beyond the range).
-template <bool SCALED>
+template <int NP, bool SHARED>
 __device__ __forceinline__ int vec_site(const VecRange& v, int i, int* part) {
-  if (SCALED) {
+  if (SHARED) {
     *part = (i >> 6) & 3;
     const int s = (i >> 8) * 64 + (i & 63);
     return s < v.nsx ? v.lo + s : -1;
   }
-  *part = i / v.nsx;
+  *part = NP == 1 ? 0 : i / v.nsx;
   return v.lo + i - *part * v.nsx;
 }
-// Components 3 part .. of site s of a vector.
-template <class SP>
+// Part `part` of the NP equal parts of site s of a vector.
+template <class SP, int NP>
 __device__ __forceinline__ void load_components(const void* v, int stride, int s, int part, cx<typename SP::R>* out) {
+  if constexpr (NP == 1) {
+    SP::load(v, stride, s, out);
+  } else {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) out[c] = SP::load_one(v, stride, s, 3 * part + c);
+    for (int c = 0; c < 3; ++c) out[c] = SP::load_one(v, stride, s, 3 * part + c);
+  }
 }
-// (SP::kScaled: every work-item of the block calls it, with s < 0 where it has nothing to store)
-template <class SP>
+// (SP::kScaled and NP = 4: every work-item of the block calls it, with s < 0 where it has nothing to store)
+template <class SP, int NP>
 __device__ __forceinline__ void store_components(void* v, int stride, int s, int part, const cx<typename SP::R>* in) {
-  if constexpr (SP::kScaled) {
+  if constexpr (NP == 1) {
+    SP::store(v, stride, s, in);
+  } else if constexpr (SP::kScaled) {
     __shared__ float smax[4][64];
     float m = 0.f;
 #pragma unroll
@@ -341,24 +354,25 @@ __device__ __forceinline__ void store_components(void* v, int stride, int s, int
   }
 }
 
-template <class SP, bool BATCH>
+template <class SP, bool BATCH, int NP>
 __global__ void __launch_bounds__(kBlock) k_cg_update(CgParam<BATCH> h) {
   using R = typename SP::R;
-  constexpr int NC = 3;
+  constexpr int NC = 12 / NP;
+  constexpr bool kShared = SP::kScaled && NP == 4;
   int label, nbx;
   const CgArgs& a = cg_args(h, &label, &nbx);
   const int Vh = h.Vh;
-  const VecRange w = vec_range<SP::kScaled>(Vh, nbx);
+  const VecRange w = vec_range<NP, kShared>(Vh, nbx);
   cx<R> q[NC] = {}, r[NC] = {};  // (zero where a work-item has no site)
   auto load = [&](int i) {
     int part;
-    const int s = vec_site<SP::kScaled>(w, i, &part);
-    if (SP::kScaled && s < 0) return;
-    load_components<SP>(a.q, Vh, s, part, q);
-    load_components<SP>(a.r, Vh, s, part, r);
+    const int s = vec_site<NP, kShared>(w, i, &part);
+    if (kShared && s < 0) return;
+    load_components<SP, NP>(a.q, Vh, s, part, q);
+    load_components<SP, NP>(a.r, Vh, s, part, r);
   };
   const int k = label + a.state->base;
-  if (a.mixed) {  // many launches of a mixed chunk are past its stop: they leave before they load
+  if (NP == 1 || a.mixed) {  // many launches of a mixed chunk or a batch are past its stop: they leave before they load
     if (k >= a.state->stop_at) return;
     asm volatile("" ::: "memory");
   }
@@ -377,15 +391,15 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(CgParam<BATCH> h) {
   for (int i = w.first; i < w.nwork; i += w.step) {
     if (i != w.first) load(i);
     int part;
-    const int s = vec_site<SP::kScaled>(w, i, &part);
-    if (!SP::kScaled || s >= 0)
+    const int s = vec_site<NP, kShared>(w, i, &part);
+    if (!kShared || s >= 0)
 #pragma unroll
       for (int m = 0; m < NC; ++m) {
         r[m].re = fma(-al, q[m].re, r[m].re);
         r[m].im = fma(-al, q[m].im, r[m].im);
         v[0] += (double)r[m].re * r[m].re + (double)r[m].im * r[m].im;
       }
-    store_components<SP>(a.r, Vh, s, part, r);
+    store_components<SP, NP>(a.r, Vh, s, part, r);
   }
   block_sum<1>(v);
   if (threadIdx.x == 0) a.pr[blockIdx.x] = v[0];
@@ -397,7 +411,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(CgParam<BATCH> h) {
 // none of them can observe a change that concerns it.
 // Every input of an element is loaded before any output is stored (x, p and r
 // are distinct arrays), so a work-item makes one round trip to memory.
-template <class SP, class SX, bool BATCH>
+template <class SP, class SX, bool BATCH, int NP>
 __global__ void __launch_bounds__(kBlock) k_cg_pupdate(CgParam<BATCH> h) {
   int label, nbx;
   const CgArgs& a = cg_args(h, &label, &nbx);
@@ -405,25 +419,26 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(CgParam<BATCH> h) {
   SolverState* stt = a.state;
   using R = typename SP::R;
   using XR = typename SX::R;
-  constexpr int NC = 3;  // components per work-item
+  constexpr int NC = 12 / NP;  // components per work-item
+  constexpr bool kShared = SP::kScaled && NP == 4;
   const void* src = a.cgls ? a.s : a.r;
-  const VecRange w = vec_range<SP::kScaled>(Vh, nbx);
+  const VecRange w = vec_range<NP, kShared>(Vh, nbx);
   const int nwork = w.nwork, i0 = w.first;
   cx<R> p[NC] = {}, q[NC] = {};  // (zero where a work-item has no site)
   cx<XR> x[NC];
   auto load = [&](int i) {
     int part;
-    const int s = vec_site<SP::kScaled>(w, i, &part);
-    if (SP::kScaled && s < 0) return;
-    load_components<SP>(a.p, Vh, s, part, p);
-    load_components<SX>(a.x, Vh, s, part, x);
-    load_components<SP>(src, Vh, s, part, q);
+    const int s = vec_site<NP, kShared>(w, i, &part);
+    if (kShared && s < 0) return;
+    load_components<SP, NP>(a.p, Vh, s, part, p);
+    load_components<SX, NP>(a.x, Vh, s, part, x);
+    load_components<SP, NP>(src, Vh, s, part, q);
   };
   // the state as the launch found it, read once (block 0 writes iters, last,
   // rr, the other parity's sum_pp, stop_at beyond this label, and maxrr only to
   // a value that leaves the decision below as it is)
   const int k = label + stt->base;
-  if (a.mixed) {  // many launches of a mixed chunk are past its stop: they leave before they load
+  if (NP == 1 || a.mixed) {  // many launches of a mixed chunk or a batch are past its stop: they leave before they load
     if (k >= stt->stop_at) return;
     asm volatile("" ::: "memory");
   }
@@ -522,8 +537,8 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(CgParam<BATCH> h) {
   const R beta = (R)(nw / old);
   for (int i = i0; i < nwork; i += w.step) {
     int part;
-    const int s = vec_site<SP::kScaled>(w, i, &part);
-    const bool on = !SP::kScaled || s >= 0;
+    const int s = vec_site<NP, kShared>(w, i, &part);
+    const bool on = !kShared || s >= 0;
     if (i != i0) load(i);
     if (on) {
       // x += alpha p with the p of this iteration
@@ -541,7 +556,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(CgParam<BATCH> h) {
           x[m] = {(XR)0, (XR)0};
         }
       }
-      store_components<SX>(a.x, Vh, s, part, x);
+      store_components<SX, NP>(a.x, Vh, s, part, x);
     }
     if (p_done) continue;
     if (on)
@@ -550,7 +565,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pupdate(CgParam<BATCH> h) {
         p[m].re = fma(beta, p[m].re, q[m].re);
         p[m].im = fma(beta, p[m].im, q[m].im);
       }
-    store_components<SP>(a.p, Vh, s, part, p);
+    store_components<SP, NP>(a.p, Vh, s, part, p);
   }
 }
 
@@ -807,27 +822,34 @@ static double cg_vec_bytes(hmc_prec prec, bool with_x, int nsp) {
   return (with_x ? 2 * sx : 0.0) + nsp * sp;
 }
 
-// Blocks of the solver-vector kernels: one share per XCD of a grid that gives
-// every work-item an element up to 2048 blocks (512 to 4096 measure the same).
-int cg_vec_blocks(int Vh) { return std::min(8 * ceil_div(4LL * Vh, 8 * kBlock), 2048); }
+int cg_vec_parts(int Vh, bool batch) { return batch && Vh >= kBatchSites ? 1 : 4; }
+// One share per XCD of a grid that gives every work-item an element up to 2048
+// blocks (512 to 4096 measure the same).
+int cg_vec_blocks(int Vh, bool batch) {
+  return std::min(8 * ceil_div((long long)cg_vec_parts(Vh, batch) * Vh, 8 * kBlock), 2048);
+}
 
 hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, const CgArgs* table, int nbatch, int j,
                             hipStream_t st) {
   // r -= alpha q: q read, r read + written
   TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, false, 3) * g.Vh * nbatch);
   if (g.stride != g.Vh || (!table && !CgOne::holds(a))) return hipErrorInvalidValue;
-  const dim3 grid(cg_vec_blocks(g.Vh), nbatch), block(kBlock);
-  auto go = [&](auto kernel_single, auto kernel_batch) {
-    if (table)
-      hipLaunchKernelGGL(kernel_batch, grid, block, 0, st, CgBatch{g.Vh, (int)grid.x, table, j});
+  const dim3 grid(cg_vec_blocks(g.Vh, table != nullptr), nbatch), block(kBlock);
+  const CgBatch batch{g.Vh, (int)grid.x, table, j};
+  auto go = [&](auto sp) {
+    using SP = decltype(sp);
+    if (!table)
+      hipLaunchKernelGGL((k_cg_update<SP, false, 4>), grid, block, 0, st, CgOne(g.Vh, grid.x, a, a.q, j));
+    else if (cg_vec_parts(g.Vh, true) == 1)
+      hipLaunchKernelGGL((k_cg_update<SP, true, 1>), grid, block, 0, st, batch);
     else
-      hipLaunchKernelGGL(kernel_single, grid, block, 0, st, CgOne(g.Vh, grid.x, a, a.q, j));
+      hipLaunchKernelGGL((k_cg_update<SP, true, 4>), grid, block, 0, st, batch);
   };
   switch (prec) {
-    case HMC_F64: go(k_cg_update<SpF64, false>, k_cg_update<SpF64, true>); break;
-    case HMC_F32: go(k_cg_update<SpF32, false>, k_cg_update<SpF32, true>); break;
-    case HMC_F16: go(k_cg_update<SpF16, false>, k_cg_update<SpF16, true>); break;
-    case HMC_BF16: go(k_cg_update<SpBF16, false>, k_cg_update<SpBF16, true>); break;
+    case HMC_F64: go(SpF64{}); break;
+    case HMC_F32: go(SpF32{}); break;
+    case HMC_F16: go(SpF16{}); break;
+    case HMC_BF16: go(SpBF16{}); break;
   }
   return hipGetLastError();
 }
@@ -837,18 +859,23 @@ hipError_t launch_cg_pupdate(const LatArg& g, hmc_prec prec, const CgArgs& a, co
   // x += alpha p, p = r + beta p: x and p read + written, r read
   TimedScope ts(TK_CG_BLAS, st, cg_vec_bytes(prec, true, 3) * g.Vh * nbatch);
   if (g.stride != g.Vh || (!table && !CgOne::holds(a))) return hipErrorInvalidValue;
-  const dim3 grid(cg_vec_blocks(g.Vh), nbatch), block(kBlock);
-  auto go = [&](auto kernel_single, auto kernel_batch) {
-    if (table)
-      hipLaunchKernelGGL(kernel_batch, grid, block, 0, st, CgBatch{g.Vh, (int)grid.x, table, j});
+  const dim3 grid(cg_vec_blocks(g.Vh, table != nullptr), nbatch), block(kBlock);
+  const CgBatch batch{g.Vh, (int)grid.x, table, j};
+  auto go = [&](auto sp, auto sx) {
+    using SP = decltype(sp);
+    using SX = decltype(sx);
+    if (!table)
+      hipLaunchKernelGGL((k_cg_pupdate<SP, SX, false, 4>), grid, block, 0, st, CgOne(g.Vh, grid.x, a, a.s, j));
+    else if (cg_vec_parts(g.Vh, true) == 1)
+      hipLaunchKernelGGL((k_cg_pupdate<SP, SX, true, 1>), grid, block, 0, st, batch);
     else
-      hipLaunchKernelGGL(kernel_single, grid, block, 0, st, CgOne(g.Vh, grid.x, a, a.s, j));
+      hipLaunchKernelGGL((k_cg_pupdate<SP, SX, true, 4>), grid, block, 0, st, batch);
   };
   switch (prec) {
-    case HMC_F64: go(k_cg_pupdate<SpF64, SpF64, false>, k_cg_pupdate<SpF64, SpF64, true>); break;
-    case HMC_F32: go(k_cg_pupdate<SpF32, SpF32, false>, k_cg_pupdate<SpF32, SpF32, true>); break;
-    case HMC_F16: go(k_cg_pupdate<SpF16, SpF32, false>, k_cg_pupdate<SpF16, SpF32, true>); break;
-    case HMC_BF16: go(k_cg_pupdate<SpBF16, SpF32, false>, k_cg_pupdate<SpBF16, SpF32, true>); break;
+    case HMC_F64: go(SpF64{}, SpF64{}); break;
+    case HMC_F32: go(SpF32{}, SpF32{}); break;
+    case HMC_F16: go(SpF16{}, SpF32{}); break;
+    case HMC_BF16: go(SpBF16{}, SpF32{}); break;
   }
   return hipGetLastError();
 }

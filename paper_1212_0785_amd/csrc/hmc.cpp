@@ -236,7 +236,7 @@ static size_t plan_fields(Fields* F, char* base, const LatArg& g, uint32_t flags
   const size_t h64 = half_bytes(Vh, HMC_F64);
   const int nbD = dslash_blocks(g, HMC_F64), nbR = blas_blocks(Vh);
   // both halves' partials, or the update's, of which there are at least eight
-  const int npart = std::max(2 * std::max(dslash_blocks_max(Vh), nbR), cg_vec_blocks(Vh));
+  const int npart = std::max(2 * std::max(dslash_blocks_max(Vh), nbR), cg_vec_blocks(Vh, false));
   const int nb_multi = std::min(nbR, 1024);
   const size_t multi = (size_t)nb_multi * 2 * 1024 + 1024;
   Fields tmp;

@@ -91,7 +91,8 @@ size_t carve_request(char* base, const LatArg& g, int prec, SolveVecs* v, void**
   s.pp[0] = (double*)c.take(np * 8);
   s.pp[1] = (double*)c.take(np * 8);
   s.pq = (double*)c.take(np * 8);
-  s.pr = (double*)c.take((size_t)cg_vec_blocks(Vh) * 8);
+  s.nbU = cg_vec_blocks(Vh, true);
+  s.pr = (double*)c.take((size_t)s.nbU * 8);
   s.red = (double*)c.take((size_t)2 * nbR * 8);
   s.nbD = nbD;
   s.nbR = nbR;

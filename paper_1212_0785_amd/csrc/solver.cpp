@@ -94,7 +94,7 @@ void build_iteration(const SolveVecs& v, int iter0, int mixed, double delta2, It
   c.pr = v.pr;
   c.n_pp = v.nbD;  // |r|^2 (CG) or |s|^2 (CGLS), both from a Dslash epilogue
   c.n_pq = v.nbD;
-  c.n_pr = cg_vec_blocks(v.g.Vh);
+  c.n_pr = v.nbU;
   c.state = v.state;
   c.iter0 = iter0;
   c.cgls = v.cgls;
@@ -629,6 +629,7 @@ hmc_status cg_solve_impl(Fields* F, void* x, const void* b, const hmc_cg_params*
   v.shape64 = dslash_run_shape(F->g, HMC_F64);
   v.nbD = dslash_shape_blocks(F->g.Vh, v.shape);
   v.nbR = F->nbR;
+  v.nbU = cg_vec_blocks(F->g.Vh, false);
   hmc_cg_stats S{};
 
   // ---- set-up in FP64: |b|^2, the even right-hand side, x = x0 (0 unless

@@ -33,7 +33,7 @@ struct SolveVecs {
   double* slot;      // device scalar (FP64 reductions land here)
   SolverState* state;
   double thr;        // stop threshold on |r|^2 of the solve
-  int nbD, nbR;
+  int nbD, nbR, nbU;  // blocks (partials) of a hop, a norm, the update
 };
 
 // Arguments of the six launches of one iteration.
