@@ -242,8 +242,10 @@ struct CgArgs {
 };
 hipError_t launch_cg_init(const LatArg& g, hmc_prec prec, const void* b, void* x, void* r, void* p, double* part,
                           int nb, hipStream_t st);
-// Blocks of the two launches below, and the |r|^2 partials of the first.
-int cg_vec_blocks(int Vh);
+// Work-items per site and blocks (of one entry) of the two launches below; the
+// first writes a |r|^2 partial per block.
+int cg_vec_parts(int Vh, bool batch);
+int cg_vec_blocks(int Vh, bool batch);
 hipError_t launch_cg_update(const LatArg& g, hmc_prec prec, const CgArgs& a, const CgArgs* table, int nbatch, int j,
                             hipStream_t st);
 hipError_t launch_cg_pupdate(const LatArg& g, hmc_prec prec, const CgArgs& a, const CgArgs* table, int nbatch, int j,
