@@ -363,29 +363,39 @@ __device__ __forceinline__ cx<R> hop_share(cx<R> acc, const cx<R> (*h)[64], int 
   return SIG > 0 ? acc + v : acc - v;
 }
 
-// Component (SPIN, c) of D psi from the eight parked half spinors, in hop order.
-template <bool DAG, int SPIN, typename R>
+// Component (SPIN, c) of D psi from the eight parked half spinors: one after the
+// other, as the one-site kernel adds them, or (PAIRS) direction by direction, as
+// the direction split does.
+template <bool DAG, bool PAIRS, int SPIN, typename R>
 __device__ __forceinline__ cx<R> hops_combine(const cx<R> (*half)[6][64], int c, int ls) {
   constexpr int SF = DAG ? +1 : -1, SB = -SF;
-  cx<R> t = {R(0), R(0)};
-  t = hop_share<0, SF, SPIN>(t, half[0], c, ls);
+  const cx<R> zero = {R(0), R(0)};
+  cx<R> t, p;
+  t = hop_share<0, SF, SPIN>(zero, half[0], c, ls);
   t = hop_share<0, SB, SPIN>(t, half[1], c, ls);
-  t = hop_share<1, SF, SPIN>(t, half[2], c, ls);
-  t = hop_share<1, SB, SPIN>(t, half[3], c, ls);
-  t = hop_share<2, SF, SPIN>(t, half[4], c, ls);
-  t = hop_share<2, SB, SPIN>(t, half[5], c, ls);
-  t = hop_share<3, SF, SPIN>(t, half[6], c, ls);
-  t = hop_share<3, SB, SPIN>(t, half[7], c, ls);
-  return t;
+  p = hop_share<1, SF, SPIN>(PAIRS ? zero : t, half[2], c, ls);
+  p = hop_share<1, SB, SPIN>(p, half[3], c, ls);
+  t = PAIRS ? t + p : p;
+  p = hop_share<2, SF, SPIN>(PAIRS ? zero : t, half[4], c, ls);
+  p = hop_share<2, SB, SPIN>(p, half[5], c, ls);
+  t = PAIRS ? t + p : p;
+  p = hop_share<3, SF, SPIN>(PAIRS ? zero : t, half[6], c, ls);
+  p = hop_share<3, SB, SPIN>(p, half[7], c, ls);
+  return PAIRS ? t + p : p;
 }
 
-template <bool DAG, typename R>
+// The sum's own rounding counts in FP32 storage, which takes the pairs (error of
+// Mhat at 18x10x14x26 4.94e-8 one after the other, 4.83e-8 in pairs; 20^3x40 35.9
+// and 36.1 us).  The narrower storages round far more than it does (FP16 2.6e-4),
+// and FP64 errs less in sequence (9.36e-17 against 9.47e-17).
+template <class SP, bool DAG, typename R>
 __device__ __forceinline__ cx<R> hops_component(const cx<R> (*half)[6][64], int spin, int c, int ls) {
+  constexpr bool kPairs = std::is_same_v<SP, SpF32>;
   switch (spin) {
-    case 0: return hops_combine<DAG, 0>(half, c, ls);
-    case 1: return hops_combine<DAG, 1>(half, c, ls);
-    case 2: return hops_combine<DAG, 2>(half, c, ls);
-    default: return hops_combine<DAG, 3>(half, c, ls);
+    case 0: return hops_combine<DAG, kPairs, 0>(half, c, ls);
+    case 1: return hops_combine<DAG, kPairs, 1>(half, c, ls);
+    case 2: return hops_combine<DAG, kPairs, 2>(half, c, ls);
+    default: return hops_combine<DAG, kPairs, 3>(half, c, ls);
   }
 }
 
@@ -588,7 +598,7 @@ __global__ void __launch_bounds__(kHopThreads) k_dslash_hops(std::conditional_t<
     for (int q = 0; q < 2; ++q) {
       if (q >= nc) break;
       const int c = c0 + q;
-      o[q] = hops_component<DAG>(half, spin, c, ls);
+      o[q] = hops_component<SP, DAG>(half, spin, c, ls);
       if (EPI != EPI_PLAIN) {
         const R a = (R)e.a, bb = (R)e.b;
         if (e.y)
@@ -686,7 +696,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_mhat_small(Lat g, const void*
   if (active)
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-      if (q < nc) odd[3 * spin + c0 + q][s] = hops_component<DAG>(half[pair], spin, c0 + q, lane);
+      if (q < nc) odd[3 * spin + c0 + q][s] = hops_component<SP, DAG>(half[pair], spin, c0 + q, lane);
   __syncthreads();
   if (active) {
 #pragma unroll
@@ -701,7 +711,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_mhat_small(Lat g, const void*
     for (int q = 0; q < 2; ++q) {
       if (q >= nc) break;
       const R bb = (R)b;
-      o[q] = hops_component<DAG>(half[pair], spin, c0 + q, lane);
+      o[q] = hops_component<SP, DAG>(half[pair], spin, c0 + q, lane);
       o[q] = {fma(bb, o[q].re, y[q].re), fma(bb, o[q].im, y[q].im)};
       if constexpr (!SP::kScaled) SP::template store_one<false>(out, g.stride, s, 3 * spin + c0 + q, o[q]);
     }

@@ -126,3 +126,22 @@ def test_batched_shapes_on_a_ragged_lattice(H, tmp_path, L, shape, prec):
         assert torch.equal(alone[0], out)
         want, _ = O.wilson_solve(lat, O.weak_field(lat, gs, eps), k, O.source(lat, kind, ss, 0), tol=1e-12)
         assert rel(to_canon(H, lat, out), want) < 1e-8
+
+
+def test_hops_add_up_in_fp32_as_precisely_as_directions(H, tmp_path):
+    """FP32 hop of one wavefront per hop against the direction split's: no larger
+    error (1% room: 850,000 numbers leave the ratio uncertain by 0.2%)."""
+    L = (14, 14, 14, 26)
+    U = synth.gauge_field(99, L, eps=0.4)
+    psi = synth.spinor(100, L)
+    want = O.dslash(L, U, psi, 0, 0)
+    F = H.Fields(L, 5.6, 0.13, flags=H.FIELDS_LOWPREC)
+    put_gauge(H, F, U)
+    src = put_spinor(H, F, psi, 1, prec=H.F32)
+    err = {}
+    for shape in (2, 4):
+        load(H, tmp_path, [f"dslash 14 14 14 26 1 {shape} 0"])
+        out = F.spinor(prec=H.F32)
+        H.hmc_wilson_dslash(F, out, src, 0, 0, H.F32)
+        err[shape] = rel(get_spinor(H, F, out, 0, prec=H.F32), want)
+    assert err[4] < 1.01 * err[2], err
