@@ -457,8 +457,8 @@ typedef enum {
 } hmc_tune_kind;
 /* Times every candidate on f's lattice and stores the fastest in the
  * table: for each storage precision the Dslash shape x link form pairs
- * (then streaming, and the site orders x workgroups per CU, for the best
- * pair)
+ * (then streaming for the best pair, and the site orders x workgroups per
+ * CU for the one-site shape in its best form)
  * where it runs, inside a solve (CG on Mhat^dag Mhat from Gaussian noise to
  * 1e-10 or 100 iterations: FP64 CG, and with HMC_FIELDS_LOWPREC
  * mixed-precision CG with that storage inside; "us" = microseconds per
@@ -470,7 +470,8 @@ typedef enum {
 hmc_status hmc_autotune(hmc_fields* f, const char* db_path, void* stream);
 hmc_status hmc_tune_load(const char* path, int32_t* n_entries);
 hmc_status hmc_tune_save(const char* path, int32_t* n_entries);
-/* Active decision for lattice L (*tuned = 1 when it comes from the table). */
+/* Active decision of one kind for lattice L, with the meanings listed above
+ * (*tuned = 1 when it comes from the table). */
 hmc_status hmc_tune_query(const int32_t* L, int32_t kind, int32_t prec, int32_t* choice, int32_t* tuned);
 
 /* ---- Mass-preconditioned (Hasenbusch) two-flavour HMC on nested time

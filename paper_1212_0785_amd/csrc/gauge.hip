@@ -510,11 +510,13 @@ __device__ __forceinline__ void gauge_force_dir(const Lat& g, const void* U, dou
 // parity, a wavefront the links of one direction (walk_site with the block
 // as the walk unit).  With compact (SU(3)) links the block first parks rows
 // 0 and 1 of its 256 own links and of the 256 links U_mu(x-mu) in LDS
-// (48 KB).  The kernel is bound by its FP64 instructions (58% of the cycles
-// of 24^3x48) and the waits for the links that feed them, so each upper
-// plaquette of the block's sites is formed once for both of its links: two
-// rows a link, 24^3x48 271 -> 244 us, 48^3x96 4.56 -> 4.25 ms.  Two of the directions take two of the six
-// planes: which wavefronts (SIMDs) have them changes from block to block.
+// (48 KB).  The kernel is bound by its FP64 instructions (VALU 58 to 60% of the
+// cycles) and the waits for the links that feed them, so each upper plaquette of
+// the block's sites is formed once for both of its links: two rows a link,
+// between the other kernels of a step 24^3x48 271 -> 244 us, 48^3x96 4.56 -> 4.36
+// to 4.41 ms (a trace's average; launched back to back 210 to 224 us and 3.98 to
+// 4.05 ms).  Two of the directions take two of the six planes: which wavefronts
+// (SIMDs) have them changes from block to block.
 // 24 KB and 128 registers, four blocks on a compute unit, lose 3%.
 template <class LK, bool NT>
 __global__ void __launch_bounds__(kBlock) k_gauge_force_sites(Lat g, const void* U, double* P, double coef_beta) {

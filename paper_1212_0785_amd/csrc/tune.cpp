@@ -1,11 +1,11 @@
 // Launch-shape and link-form decisions and their persisted tuning table
 // (the auto-tuner of Sec. 4, for the choices this library offers): per
 // lattice and storage, the Dslash shape (one site per work-item, two
-// wavefronts per site, or one wavefront per hop), its link streaming, site order and workgroups per
-// CU, the staple-force shape (one link per work-item, plane split, or four
-// directions of 64 sites per block in the tiled walk), and
-// the compact link form of the hop and staple kernels (two rows, or row 0
-// and column 2).
+// wavefronts per 64 sites, or one wavefront per hop), its link streaming, site
+// order and workgroups per CU, the staple-force shape (one link per work-item,
+// plane split, or four directions of 64 sites per block in the tiled walk), and
+// the compact link form of the hop and staple kernels (two rows, or row 0 and
+// column 2).
 //
 // Precedence: environment override (HMC_DSLASH_SPLIT, HMC_GFORCE_PLANES,
 // HMC_LINK_FORM, HMC_LINK_STREAM, HMC_DSLASH_ORDER, HMC_DSLASH_OCC) > tuned
@@ -192,7 +192,7 @@ int dslash_link_form(const LatArg& g, hmc_prec prec) {
   if (t > 0) return t;
   // Two rows below 2^20 half-lattice sites: they rebuild a reunitarised FP64
   // link bit for bit, row 0 and column 2 do not (error of Mhat at 24^3x44, two
-  // rows / row 0 + column 2: FP64 9.34e-17 / 9.92e-17, FP32 4.94e-8 / 5.08e-8,
+  // rows / row 0 + column 2: FP64 9.34e-17 / 9.92e-17, FP32 4.83e-8 / 4.97e-8,
   // FP16 2.78e-4 / 2.80e-4).  From there a sixth fewer link bytes decide.
   // Measured (Mhat, us, the same order): FP64 20^3x40 70.1 / 64.3, 24^3x44 140 /
   // 128, 28^3x60 298 / 273; FP32 20^3x40 35.6 / 33.4, 28^3x60 171 / 159; FP16
@@ -214,12 +214,14 @@ bool dslash_link_stream(const LatArg& g, hmc_prec prec) {
   const int t = tune_lookup(g.L, TUNE_DSLASH_STREAM, prec);
   if (t >= 0) return t != 0;
   // Streaming pays once the links a hop reads no longer stay in the 256 MB
-  // last-level cache from one hop to the next, beside the vectors; before
-  // that the hints only bypass it.  Measured (Mhat, plain / streamed, us, with
-  // the links' MB): FP64 20^3x40 (102 MB) 70 / 79, 24^3x48 (212) 161 / 157,
-  // 32^3x64 (671) 575 / 480; FP32 24^3x48 (106) 68 / 85, 32^3x64 (336) 288 /
-  // 260; BF16 32^3x64 (168) 138 / 145 on links just used, 149 / 146 on others
-  // and 575 / 572 per iteration of a solve, 40^3x80 (410) 356 / 324
+  // last-level cache from one hop to the next, beside the vectors; before that
+  // the hints only bypass it.  Measured (Mhat, us, plain / streamed, in the link
+  // form and shape of the rules, with the ten-real links' MB): FP64 20^3x40 (102
+  // MB) 70.1 / 75.6, 20x24x24x44 (162) 114 / 115 and 281 / 280 per iteration of a
+  // solve, 24^3x44 (195) 145 / 140, 32^3x64 (671) 565 / 445; FP32 24^3x44 (97) 66.8
+  // / 81.4, 24x28x28x52 (157) 123 / 127 and 396 / 394, 28^3x60 (211) 180 / 171,
+  // 32^3x64 (336) 298 / 258; BF16 32^3x64 (168) 140 / 141 and 538 / 537, 40^3x80
+  // (410) 358 / 325
   return compact_link_bytes(g, prec) >= 150e6;
 }
 
@@ -269,16 +271,23 @@ int dslash_shape(const LatArg& g, hmc_prec prec) {
   const int t = tune_lookup(g.L, TUNE_DSLASH, prec);
   if (t > 0) return t;
   // One wavefront per hop until the launch fills the chip so many times over
-  // that the one-site kernel's smaller traffic wins: FP64 up to 36x28x32x72
-  // sites, whence the tiled order keeps neighbours in L2; the narrower
-  // storages sooner, whose hop is bound by its instructions (measured, Mhat in
-  // us, 1 / 2 / 4: FP64 16^3x32 35 / 32 / 29, 24^3x48 184 / 164 / 154, 32^3x64
-  // 529 / 486 / 462, 36x28x32x72 539 / 563 / 526, 40^3x80 1247 / 1322 / 1280;
-  // FP32 16^3x32 21.3 / 19.3 / 17.4, 24^3x48 88 / 74 / 68, 32^3x64 261 / 260 /
-  // 254; BF16 16^3x32 15.9 / 14.7 / 12.4, 32^3x64 138 / 148 / 151; in a solve,
-  // whose p-update adds four times the partial sums of the split shapes, us
-  // per iteration: FP32 24^3x48 291 / 271 / 270, 32^3x64 844 / 894 / 887; FP16
-  // 24^3x48 203 / 206 / 215; BF16 186 / 193 / 196)
+  // that the one-site kernel's smaller traffic wins, for the narrower storages
+  // sooner, whose hop is bound by its instructions and whose p-update adds four
+  // times the partial sums of the split shapes.  Measured with the link form and
+  // streaming of the rules, us, shapes 1 / 2 / 4, Mhat and per iteration of a
+  // solve: FP64 20^3x40 95 / 79 / 70, 224 / 195 / 172; 24^3x44 160 / 150 / 140, 382
+  // / 367 / 344; 28^3x60 347 / 318 / 298, 846 / 808 / 772; 32^3x64 477 / 472 / 445,
+  // 1225 / 1204 / 1156; 40^3x80, where the tiled order keeps neighbours in L2, 1256
+  // / 1310 / 1292, 3097 / 3284 / 3244.  (Lattices that do not admit that order go
+  // the same way without gaining by it: 36^3x72 872 / 805 / 768, 2094 / 2009 / 1947;
+  // 40^3x84 1385 / 1288 / 1238, 3394 / 3319 / 3245.)  FP32 20^3x40 43 / 41 / 36, 133
+  // / 134 / 122; 24x28x28x52 139 / 136 / 127, 402 / 416 / 394; 28^3x60 188 / 183 /
+  // 171, 546 / 562 / 536; 32^3x64 258 / 261 / 247, 796 / 850 / 825.  FP16 20^3x40 32
+  // / 31 / 26, 117 / 121 / 110; 20x24x24x44 38 / 42 / 38, 147 / 163 / 155; 28^3x60
+  // 90 / 82 / 86, 365 / 383 / 383.  BF16 20^3x40 28 / 26 / 24, 107 / 109 / 103;
+  // 20x24x24x44 34 / 36 / 34, 136 / 147 / 143; 28^3x60 82 / 74 / 75, 342 / 362 / 360.
+  // Two wavefronts (2) lead nowhere in a solve; tables and overrides
+  // may ask for them.
   // (below one block choice 1 runs as 4: dslash_run_shape)
   if (prec == HMC_F64) return g.Vh < kThreads ? 1 : g.Vh < 3 << 19 ? 4 : 1;
   return g.Vh < (prec == HMC_F32 ? 1 << 19 : 1 << 18) ? 4 : 1;
