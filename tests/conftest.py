@@ -11,10 +11,12 @@ def pytest_configure(config):
     config.addinivalue_line("markers", "slow: long-running CPU test")
 
 
-# Modules that load tuning entries for extents which other tests take as
-# untuned.  Entries last as long as the process, so these run after the others.
-LEAVES_ENTRIES = ("test_gpu_hops.py",)
+# Tuning entries last as long as the process: the modules that query the built-in
+# rules run before any other loads entries for their extents, and the module that
+# loads entries for extents which other tests take as untuned runs last.
+FIRST = ("test_tune.py", "test_tune_rules.py")
+LAST = ("test_gpu_hops.py",)
 
 
 def pytest_collection_modifyitems(items):
-    items.sort(key=lambda item: item.path.name in LEAVES_ENTRIES)
+    items.sort(key=lambda item: (item.path.name in LAST) - (item.path.name in FIRST))
